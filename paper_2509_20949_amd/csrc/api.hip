@@ -340,7 +340,7 @@ static smcx_status enqueue_phase(smcx_ctx* c, uint32_t s, int col, int groups)
         if (!st) st = ctx_hip(c, hipEventRecord(e0, c->stream), "hipEventRecord");
         if (st) return st;
     }
-    hipError_t e = launch_sweep_phase(c->h_lat.lattice, c->d_lat, nullptr, groups, (int)s, col, c->kmax, c->smax,
+    hipError_t e = launch_sweep_phase(c->h_lat.lattice, c->d_lat, nullptr, groups, c->h_lat.blocks_per_colour, (int)s, col, c->kmax, c->smax,
                                       c->stream, c->slab, c->wpg);
     if (e != hipSuccess) return ctx_hip(c, e, "sweep_phase launch");
     if (c->profiling) {

@@ -247,11 +247,14 @@ smcx_status smcx_batch_run(smcx_batch* b, const int32_t* n_sweeps)
     if (!b->graph || key != b->graph_key) {
         std::vector<WorkItem> items;
         std::vector<int32_t> prefix_end(b->n);   // items of order[0..k]
+        std::vector<int32_t> prefix_blocks(b->n);
+        int32_t blocks = 0;
         for (int k = 0; k < b->n; ++k) {
             const int r = order[k];
             const int wpg = waves_per_group(b->h_lats[r].lattice);
             for (int g = 0; g < b->groups[r]; ++g) items.push_back(WorkItem{r, g * wpg});
             prefix_end[k] = (int32_t)items.size();
+            prefix_blocks[k] = blocks += b->h_lats[r].blocks_per_colour;
         }
         if (!items.empty()) {
             st = bhip(b, hipMemcpy(b->d_items_run, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice),
@@ -268,8 +271,8 @@ smcx_status smcx_batch_run(smcx_batch* b, const int32_t* n_sweeps)
             while (active > 0 && n_sweeps[order[active - 1]] <= t) --active;
             const int n_groups = prefix_end[active - 1];
             for (int c = 0; c < 8 && le == hipSuccess; ++c)
-                le = launch_sweep_phase(b->lattice, b->d_lats, b->d_items_run, n_groups, t, c, b->kmax, b->smax,
-                                        b->stream);
+                le = launch_sweep_phase(b->lattice, b->d_lats, b->d_items_run, n_groups, prefix_blocks[active - 1], t, c,
+                                        b->kmax, b->smax, b->stream);
         }
         hipGraph_t g = nullptr;
         hipError_t ce = hipStreamEndCapture(b->stream, &g);
@@ -296,7 +299,8 @@ smcx_status smcx_batch_run_unbatched(smcx_batch* b, const int32_t* n_sweeps)
         for (int t = 0; t < n_sweeps[r]; ++t)
             for (int c = 0; c < 8; ++c) {
                 hipError_t e = launch_sweep_phase(b->lattice, b->d_lats, b->d_items_static + b->first_static[r],
-                                                  b->groups[r], t, c, b->kmax, b->smax, b->stream);
+                                                  b->groups[r], b->h_lats[r].blocks_per_colour, t, c, b->kmax,
+                                                  b->smax, b->stream);
                 if (e != hipSuccess) return bhip(b, e, "sweep_phase launch");
             }
     finish_run(b, n_sweeps);

@@ -11,52 +11,21 @@
 //   program order, so no barrier separates the rounds.
 #include <type_traits>
 
-#include "device_common.h"
+#include "bcc_block.h"
 
 namespace smcx {
 
-// ---------------------------------------------------------------------------
-// Species codes in LDS.  A site of species v is stored as (F + 32) * v, with
-// F = 5 bits per species field when KMAX <= 6 and F = 4 otherwise: the low 5
-// bits (the only bits a 32-bit shift reads) equal F * v, the top 3 bits equal
-// v.  One shift-add per neighbour then counts species into packed fields.
-template <int KMAX> struct Field { static constexpr int F = KMAX <= 6 ? 5 : 4; };
+// Waves per SIMD the BCC sweep kernel is compiled for (registers); LDS
+// (4 block images and the weight planes per workgroup) admits 5 workgroups
+// of 4 waves per CU.
+constexpr int kSweepWavesPerSimd = 5;
 
-__device__ __forceinline__ uint32_t encode4(uint32_t species, int F)
-{
-    // up to four species bytes v_k -> bytes (F+32) v_k: no carries, as
-    // (F+32) v <= 255 for every species the field width admits (all four
-    // bytes are used, so no 24-bit multiply)
-    return (species << 5) + species * (uint32_t)F;
-}
-
-// LDS layout of one block (see smcx_internal.h): corner array at offset 0,
-// body array at kArr.  Local cell (x, y, z):
-//   corner: (z+1)*kPP + (y+1)*kP + (x+1)       x in -1..13
-//   body:   kArr + (z+2)*kPP + (y+2)*kP + (x+2) x in -2..12
 // Offsets of the first shell from a corner site (body sites at cell offsets
 // {-1,0}^3) and from a body site (corner sites at {0,+1}^3):
 constexpr int kS1Corner = kArr;                      // + ex + ey*kP + ez*kPP, e in {0,1}
 constexpr int kS1Body = -kArr - (kPP + kP + 1);      // + ex + ey*kP + ez*kPP, e in {0,1}
 
 template <int SUB> __device__ __forceinline__ constexpr int s1base() { return SUB == 0 ? kS1Corner : kS1Body; }
-
-// Waves per SIMD the BCC sweep kernel is compiled for (registers); LDS
-// (4 block images and the weight planes per workgroup) admits 5 workgroups
-// of 4 waves per CU.
-constexpr int kSweepWavesPerSimd = 5;
-// Rows whose loads a lane issues together when staging a block (registers
-// bound it: one aligned word per row once the two loads are joined).
-constexpr int kStageBatch = 16;
-
-// Weight planes of the BCC kernel: row (a, b) at position a*KMAX + b of a
-// 64-entry plane, so that the position of any two 3-bit codes (a lane
-// without a site may decode a stale halo byte) stays inside its plane.  The
-// KMAX^2 rows of real species then lie in distinct LDS banks (positions
-// 8a + b, one multiply fewer, put species 4 and 0 of K = 5 on the same
-// banks: 16 % of the LDS cycles went to those conflicts).
-constexpr int kPlane = 64;
-static_assert(7 * kMaxK + 7 < kPlane, "weight plane too narrow");
 
 // Shell offsets inside one sublattice array.
 __device__ __forceinline__ constexpr int s2off(int k)
@@ -70,7 +39,6 @@ __device__ __forceinline__ constexpr int s3off(int k)
          : k == 4 ? 1 + kPP : k == 5 ? 1 - kPP : k == 6 ? -1 + kPP : k == 7 ? -1 - kPP
          : k == 8 ? kP + kPP : k == 9 ? kP - kPP : k == 10 ? -kP + kPP : -kP - kPP;
 }
-
 
 // Counts of the second and third shells of the site at LDS byte a (its own
 // sublattice), added to h[1] and h[2]; the codes of the 6 second and 12
@@ -414,7 +382,6 @@ __global__ __launch_bounds__(kWave * WPG) __attribute__((amdgpu_waves_per_eu(kSw
 void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __restrict__ items, int n_groups,
                         int t, int colour)
 {
-    constexpr int F = Field<KMAX>::F;
     // One LDS buffer: the weight planes at offset 0 (so a plane's LDS offset
     // fits the st64 immediates of ds_read2st64_b32 and row addresses need no
     // base added), then the block images.
@@ -449,218 +416,12 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     f += wave;
     if (f >= D.blocks_per_colour) return;   // no later barrier
 
-    // block coordinates: same-colour blocks are every other block per axis
-    const int hx = D.nb[0] >> 1, hy = D.nb[1] >> 1;
-    const int kx = 2 * (f % hx) + (colour & 1);
-    const int ky = 2 * ((f / hx) % hy) + ((colour >> 1) & 1);
-    const int kz = 2 * (f / (hx * hy)) + ((colour >> 2) & 1);
-    const int Lx = D.L[0], Ly = D.L[1], Lz = D.L[2];
-
-    // origin shift of sweep s (same for every wave of the sweep)
-    uint32_t sh[4] = {0u, 0u, s, 8u};
-    philox4x32_10(sh, D.key[0], D.key[1]);
-    const int ox = (int)(((uint64_t)sh[0] * (uint32_t)Lx) >> 32);
-    const int oy = (int)(((uint64_t)sh[1] * (uint32_t)Ly) >> 32);
-    // a z-slab keeps its blocks aligned to its boundaries: no z shift
-    constexpr bool slab = SLAB;
-    const int oz = slab ? 0 : (int)(((uint64_t)sh[2] * (uint32_t)Lz) >> 32);
-
-    const int x0 = block_lo(kx, Lx, D.nb[0]), wx = block_lo(kx + 1, Lx, D.nb[0]) - x0;
-    const int y0 = block_lo(ky, Ly, D.nb[1]), wy = block_lo(ky + 1, Ly, D.nb[1]) - y0;
-    const int z0 = block_lo(kz, Lz, D.nb[2]), wz = block_lo(kz + 1, Lz, D.nb[2]) - z0;
-    // global coordinate of local cell 0
-    const int gx0 = wrap_add(x0 + ox, Lx), gy0 = wrap_add(y0 + oy, Ly), gz0 = wrap_add(z0 + oz, Lz);
-
+    const uint32_t k0 = D.key[0], k1 = D.key[1];
+    const BccDraws pb = bcc_draws(s, colour, k0, k1, lane);
+    const BccBlock B = bcc_block<SLAB>(D, f, s, colour, pb);
     uint8_t* lat = s_lat + wave * kWaveLds;
-    uint8_t* __restrict__ g = D.species;
-    // plane of the lattice array that holds local z plane lz of the block:
-    // periodic wrap, or on a slab the plane two further on (the array starts
-    // with the two halo planes below the slab)
-    auto zplane = [&](int lz) -> int { return slab ? gz0 + lz + 2 : wrap_add(gz0 + lz, Lz); };
-
-    // cell ids (and, on a slab, global cell ids) fit 32 bits and the 24-bit
-    // multiplier (the usual case)
-    const uint32_t LxLy = (uint32_t)Lx * (uint32_t)Ly;
-    const uint64_t zspan = slab ? (uint64_t)Lz + 4 + D.z_off : (uint64_t)Lz;
-    const bool narrow = LxLy < (1u << 24) && (uint64_t)LxLy * zspan < (1ull << 32);
-
-    // species bytes -> LDS codes for this lattice's form of the weight rows
     const bool dot_codes = KMAX <= 5 && D.drop_last == kWtabDot;
-    auto encode = [&](uint32_t v) -> uint32_t {
-        if constexpr (KMAX <= 5) {
-            if (dot_codes) return encode4_dot<KMAX>(v);
-        }
-        return encode4(v, F);
-    };
-    // The same map as a byte table for v_perm_b32, code_hi:code_lo = codes
-    // of species 7..0 (species >= KMAX never occur: table byte 0).
-    uint32_t code_lo = 0u, code_hi = 0u;
-#pragma unroll
-    for (int v = 0; v < 8; ++v) {
-        const uint32_t c = v < KMAX ? encode((uint32_t)v) & 0xffu : 0u;
-        if (v < 4) code_lo |= c << (8 * v);
-        else code_hi |= c << (8 * (v - 4));
-    }
-    // v_perm_b32 reads at most one scalar operand: hold one word in a vector
-    // register for the whole staging rather than copying it there per row
-    asm volatile("" : "+v"(code_lo));
-
-    // A plane of the lattice (or the slab buffer) and its byte count from
-    // there to the end of the buffer: the resource of the plane's rows.
-    const uint64_t plane_bytes = 2ull * LxLy;
-    const uint64_t buf_bytes = plane_bytes * (uint64_t)(slab ? Lz + 4 : Lz);
-    const bool plane32 = plane_bytes < (1ull << 31);   // a row's byte offsets fit 31 bits
-
-    // ---- stage block + halo: local cells -2..w+1 on each axis ----
-    // Fast path (the block's x-range does not cross the periodic boundary):
-    // 8 lanes per row, each taking cells lx0, lx0 + 1 (lx0 = 2 (lane & 7) - 2),
-    // i.e. the bytes corner, body, corner, body at byte `at` of the row; it
-    // loads the aligned dwords at `at & ~3` and 4 bytes on and aligns them.
-    // Lane row lr = lane >> 3 takes rows ly = lr - 2 + 8 h (h = 0, 1) of each
-    // plane lz = -2 .. 13.  Per lane, the in-plane byte offsets and LDS
-    // positions of its two rows are set up once; a row adds only its plane,
-    // which is wave-uniform (the buffer resource's base, scalar registers).
-    // All 16 loads of a batch are issued before any LDS write.  Rows, planes
-    // and cells past the halo (w < 12) load an in-range cell and write it to
-    // image positions past w + 1, which no trial with a site and no
-    // write-back reads; only positions outside the 15^3 arrays (corner -2,
-    // body 13) are not written.  Every load stays inside the row's plane.
-    if (plane32 && gx0 >= 3 && gx0 + wx + 4 <= Lx) {
-        const int c8 = lane & 7, lr = lane >> 3;
-        const int lx0 = 2 * c8 - 2;
-        const int lxa = lx0 <= wx + 1 ? lx0 : -2;   // cells the lane loads
-        uint32_t yoff[2];
-        int cl[2];
-        bool mc0[2], mc1[2], mb0[2], mb1[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int ly = lr - 2 + 8 * h;
-            const uint32_t gy = (uint32_t)wrap_add(gy0 + min(ly, wy + 1), Ly);
-            yoff[h] = 2u * (gy * (uint32_t)Lx + (uint32_t)(gx0 + lxa));
-            cl[h] = (ly + 1) * kP + (lx0 + 1);      // corner(lx0, ly, -1), less a plane
-            mc0[h] = ly >= -1 && c8 >= 1;
-            mc1[h] = ly >= -1;
-            mb0[h] = ly <= 12;
-            mb1[h] = ly <= 12 && c8 <= 6;
-        }
-#pragma unroll
-        for (int it0 = 0; it0 < 32; it0 += kStageBatch) {
-            uint32_t v[kStageBatch];
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int it = it0 + u, h = it & 1, lz = (it >> 1) - 2;
-                const uint64_t zb = plane_bytes * (uint32_t)zplane(min(lz, wz + 1));
-                const uint64_t base = zb & ~(uint64_t)3;
-                const __amdgpu_buffer_rsrc_t r = byte_rsrc(g + base, buf_bytes - base);
-                const uint32_t at = yoff[h] + ((uint32_t)zb & 2u);
-                const uint32_t A = at & ~3u;
-                v[u] = __builtin_amdgcn_perm(code_hi, code_lo,
-                                             __builtin_amdgcn_alignbyte(bload32(r, A + 4), bload32(r, A), at));
-            }
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int it = it0 + u, h = it & 1, lz = (it >> 1) - 2;
-                uint8_t* p = lat + cl[h] + (lz + 1) * kPP;   // corner(lx0, ly, lz)
-                uint8_t* q = p + (kArr + kPP + kP + 1);      // body(lx0, ly, lz)
-                const uint32_t w8 = v[u] >> 8;
-                if (lz >= -1) {
-                    if (mc0[h]) p[0] = (uint8_t)v[u];
-                    if (mc1[h]) p[1] = (uint8_t)(v[u] >> 16);
-                }
-                if (lz <= 12) {
-                    if (mb0[h]) q[0] = (uint8_t)w8;
-                    if (mb1[h]) q[1] = (uint8_t)(w8 >> 16);
-                }
-            }
-        }
-    } else if (plane32) {
-        // The x-range crosses the periodic boundary: the rows and LDS
-        // positions of the fast path, but each lane loads its two cells
-        // separately, one 16-bit load each at its own wrapped x, so that a
-        // pair may straddle the boundary.  The plane's byte remainder
-        // (zb & 2) goes into the scalar offset of both loads.
-        const int c8 = lane & 7, lr = lane >> 3;
-        const int lx0 = 2 * c8 - 2;
-        const int lxa = lx0 <= wx + 1 ? lx0 : -2;   // cells the lane loads
-        // gx0 + lxa + 1 <= (Lx - 1) + (wx + 2) < 2 Lx, as wx + 2 <= Lx
-        const uint32_t gxa = (uint32_t)wrap_add(gx0 + lxa, Lx), gxb = (uint32_t)wrap_add(gx0 + lxa + 1, Lx);
-        uint32_t oa[2], ob[2];
-        int cl[2];
-        bool mc0[2], mc1[2], mb0[2], mb1[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int ly = lr - 2 + 8 * h;
-            const uint32_t row = (uint32_t)wrap_add(gy0 + min(ly, wy + 1), Ly) * (uint32_t)Lx;
-            oa[h] = 2u * (row + gxa);
-            ob[h] = 2u * (row + gxb);
-            cl[h] = (ly + 1) * kP + (lx0 + 1);
-            mc0[h] = ly >= -1 && c8 >= 1;
-            mc1[h] = ly >= -1;
-            mb0[h] = ly <= 12;
-            mb1[h] = ly <= 12 && c8 <= 6;
-        }
-#pragma unroll
-        for (int it0 = 0; it0 < 32; it0 += kStageBatch) {
-            uint32_t v[kStageBatch];
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int it = it0 + u, h = it & 1, lz = (it >> 1) - 2;
-                const uint64_t zb = plane_bytes * (uint32_t)zplane(min(lz, wz + 1));
-                const uint64_t base = zb & ~(uint64_t)3;
-                const __amdgpu_buffer_rsrc_t r = byte_rsrc(g + base, buf_bytes - base);
-                const int so = (int)((uint32_t)zb & 2u);
-                const uint32_t a = __builtin_amdgcn_raw_buffer_load_b16(r, (int)oa[h], so, 0);
-                const uint32_t b = __builtin_amdgcn_raw_buffer_load_b16(r, (int)ob[h], so, 0);
-                v[u] = __builtin_amdgcn_perm(code_hi, code_lo, a | b << 16);
-            }
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int it = it0 + u, h = it & 1, lz = (it >> 1) - 2;
-                uint8_t* p = lat + cl[h] + (lz + 1) * kPP;
-                uint8_t* q = p + (kArr + kPP + kP + 1);
-                const uint32_t w8 = v[u] >> 8;
-                if (lz >= -1) {
-                    if (mc0[h]) p[0] = (uint8_t)v[u];
-                    if (mc1[h]) p[1] = (uint8_t)(v[u] >> 16);
-                }
-                if (lz <= 12) {
-                    if (mb0[h]) q[0] = (uint8_t)w8;
-                    if (mb1[h]) q[1] = (uint8_t)(w8 >> 16);
-                }
-            }
-        }
-    } else {
-        // planes of 2 GiB or more: one cell (two bytes) per lane, rows
-        // r = (lane >> 4) + 4 it, 64-bit addresses; all 64 loads of a lane
-        // are issued before any LDS write, as on the fast path (lanes and
-        // rows outside the halo load a clamped in-range cell)
-        const int lx = (lane & 15) - 2;
-        const bool okx = lx <= wx + 1;
-        const int gx = wrap_add(gx0 + (okx ? lx : -2), Lx);
-#pragma unroll
-        for (int it0 = 0; it0 < 64; it0 += 2 * kStageBatch) {
-            uint32_t v2[2 * kStageBatch];
-#pragma unroll
-            for (int u = 0; u < 2 * kStageBatch; ++u) {
-                const int it = it0 + u;
-                const int ly = min((lane >> 4) + 4 * (it & 3) - 2, wy + 1), lz = min((it >> 2) - 2, wz + 1);
-                const int gy = wrap_add(gy0 + ly, Ly);
-                const size_t cell = ((size_t)zplane(lz) * Ly + gy) * Lx + gx;
-                v2[u] = gload<uint16_t>(g + 2 * cell);
-            }
-#pragma unroll
-            for (int u = 0; u < 2 * kStageBatch; ++u) {
-                const int it = it0 + u;
-                const int ly = (lane >> 4) + 4 * (it & 3) - 2, lz = (it >> 2) - 2;
-                if (!okx || ly > wy + 1 || lz > wz + 1) continue;
-                const uint32_t v = encode(v2[u]);
-                if (lx >= -1 && ly >= -1 && lz >= -1)
-                    lat[(lz + 1) * kPP + (ly + 1) * kP + (lx + 1)] = (uint8_t)v;
-                if (lx <= wx && ly <= wy && lz <= wz)
-                    lat[kArr + (lz + 2) * kPP + (ly + 2) * kP + (lx + 2)] = (uint8_t)(v >> 8);
-            }
-        }
-    }
+    bcc_stage<KMAX, WavePitch, SLAB, 1>(B, lat, lane, 0, dot_codes, [] {});
 
     // ---- 27 residue classes x 2 sublattices = 54 rounds ----
     // Lane (ix, iy, iz) takes local cell (rx + 3 ix, ry + 3 iy, rz + 3 iz) of
@@ -676,34 +437,8 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     lane_cell(lane, ix, iy, iz);
     const int lane_c = (3 * iz + 1) * kPP + (3 * iy + 1) * kP + (3 * ix + 1);
     constexpr int kBodyFromCorner = kArr + kPP + kP + 1;
-    const uint32_t k0 = D.key[0], k1 = D.key[1];
     uint32_t base_lo, base_hi;
-    {
-        // a lane that holds a site has gx0 + 3 ix < 2 Lx: one conditional
-        // subtraction wraps it (other lanes only feed their draws to no trial)
-        uint32_t bx = (uint32_t)(gx0 + 3 * ix), by = (uint32_t)(gy0 + 3 * iy), bz = (uint32_t)(gz0 + 3 * iz);
-        bx = min(bx, bx - (uint32_t)Lx);
-        by = min(by, by - (uint32_t)Ly);
-        bz = slab ? bz + D.z_off : min(bz, bz - (uint32_t)Lz);   // a slab's cells are numbered globally
-        const uint64_t cell = narrow ? (uint64_t)(__umul24(bz, LxLy) + __umul24(by, (uint32_t)Lx) + bx)
-                                     : ((uint64_t)bz * (uint32_t)Ly + by) * (uint32_t)Lx + bx;
-        base_lo = (uint32_t)cell;
-        base_hi = (uint32_t)(cell >> 32);
-    }
-    uint64_t yz_lo, yz_hi, x_bits;   // partner steps, wave-uniform
-    {
-        uint32_t R[4] = {0u, 0u, s, 32u + (uint32_t)colour};
-        philox4x32_10(R, k0, k1);
-        // (readfirstlane returns int: widen through uint32_t, not by sign)
-        yz_lo = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(R[0]) |
-                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(R[1]) << 32;
-        yz_hi = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(R[2]) |
-                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(R[3]) << 32;
-        uint32_t X[4] = {0u, 0u, s, 40u + (uint32_t)colour};
-        philox4x32_10(X, k0, k1);
-        x_bits = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(X[0]) |
-                 (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(X[1]) << 32;
-    }
+    bcc_base_cell<SLAB>(B, D.z_off, ix, iy, iz, base_lo, base_hi);
     int64_t dEsum = 0;
     uint32_t nacc = 0;
     const float ln2kT = (float)g_tab[kTabLn2kT];
@@ -714,7 +449,7 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
         constexpr int MODE = decltype(mode_tag)::value;
         // rounds of residue class m (corner then body) with draws uc, ub, the
         // y/z steps of sub-colours 2m, 2m+1 in b4 (bits 0-1, 2-3) and their x
-        // steps in bits 2m, 2m+1 of x_bits
+        // steps in bits 2m, 2m+1 of pb.x
         // Carries (three shells only: they hand on second and third
         // neighbours): corner -> body of every class, and body -> corner of
         // the next class when that is one cell on in x (rx = 1, 2).
@@ -722,9 +457,9 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
         Carry cy;
         auto rounds = [&](int m, uint32_t uc, uint32_t ub, uint32_t b4) {
             const int rx = m % 3, ry = (m / 3) % 3, rz = m / 9;
-            const bool valid = (3 * ix < wx - rx) & (3 * iy < wy - ry) & (3 * iz < wz - rz);
+            const bool valid = (3 * ix < B.wx - rx) & (3 * iy < B.wy - ry) & (3 * iz < B.wz - rz);
             const int ac = lane_c + (rz * kPP + ry * kP + rx);
-            const uint32_t xb = (uint32_t)(x_bits >> (2 * m));
+            const uint32_t xb = (uint32_t)(pb.x >> (2 * m));
             const int e0 = (int)(xb & 1u) | (int)(b4 & 3u) << 1;
             const int e1 = (int)((xb >> 1) & 1u) | (int)((b4 >> 2) & 3u) << 1;
             if (CARRY && rx == 0) {   // wave-uniform: no carry into the first class of an x row
@@ -751,7 +486,7 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
             w[0] = base_lo; w[1] = base_hi; w[2] = s; w[3] = (uint32_t)colour + 256u * (uint32_t)(k + 1);
             philox4x32_10(w, k0, k1);
             // partner bits of sub-colours 4k .. 4k+3: bits 8k .. 8k+7
-            uint32_t bits = (uint32_t)(8 * k < 64 ? yz_lo >> (8 * k) : yz_hi >> (8 * k - 64));
+            uint32_t bits = (uint32_t)(8 * k < 64 ? pb.yz_lo >> (8 * k) : pb.yz_hi >> (8 * k - 64));
             const int nj = k < 13 ? 2 : 1;
 #pragma nounroll
             for (int j = 0; j < nj; ++j) {
@@ -763,7 +498,7 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
         }
     };
     if constexpr (KMAX <= 5) {
-        if (D.drop_last == kWtabDot)
+        if (dot_codes)
             all_rounds(std::integral_constant<int, kWtabDot>{});
         else
             all_rounds(std::integral_constant<int, kWtabFull>{});
@@ -774,91 +509,7 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
             all_rounds(std::integral_constant<int, kWtabFull>{});
     }
 
-    // ---- write back ----
-    // A trial changes only corner cells 0..w and body cells -1..w-1 of the
-    // block (its sites and their first neighbours).  Row path (planes under
-    // 2 GiB): every cell of the box -1..w on each axis is written
-    // whole (corner and body byte, one 16-bit store), the cells no trial
-    // could change with the value staged from them.  That is the value they
-    // still hold: no block of the same colour changes them (same-colour
-    // blocks are one block of width >= 2 apart along some axis, and their
-    // changes reach one cell beyond their own cells), and the cells of the
-    // box are distinct (L >= w + 2 on each axis: at least 2 blocks of width
-    // >= 2).  16 lanes per row (lx = (lane & 15) - 1) and 4 rows per
-    // instruction: lane row lys = lane >> 4 takes rows ly = 4 yg + lys - 1
-    // (yg = 0..3) of each plane lz = -1..w.  Per lane, the in-plane byte
-    // offsets and LDS positions of its four rows are set up once; lanes past
-    // the box read a clamped in-image cell and store nothing.  A lane's x is
-    // wrapped once here, so blocks whose x-range crosses the periodic
-    // boundary take this path too (same-colour blocks are as far apart
-    // across the boundary as anywhere else, nb being even).
-    if (plane32) {
-        const int lx = (lane & 15) - 1, lys = lane >> 4;
-        const int lxc = min(lx, wx);
-        uint32_t yo[4];
-        int cw[4];
-        bool ok[4];
-#pragma unroll
-        for (int yg = 0; yg < 4; ++yg) {
-            const int ly = 4 * yg + lys - 1, lyc = min(ly, wy);
-            ok[yg] = lx <= wx && ly <= wy;
-            const uint32_t gy = (uint32_t)wrap_add(gy0 + lyc, Ly);
-            yo[yg] = 2u * (gy * (uint32_t)Lx + (uint32_t)wrap_add(gx0 + lxc, Lx));
-            cw[yg] = (lyc + 1) * kP + (lxc + 1);   // corner(lxc, lyc, -1), less a plane
-        }
-#pragma unroll
-        for (int lz = -1; lz <= kMaxBlock; ++lz) {
-            if (lz > wz) continue;   // (wave-uniform)
-            const uint64_t zb = plane_bytes * (uint32_t)zplane(lz);
-            const __amdgpu_buffer_rsrc_t r = byte_rsrc(g + zb, buf_bytes - zb);
-            uint32_t e[4];
-#pragma unroll
-            for (int yg = 0; yg < 4; ++yg) {
-                const uint8_t* p = lat + cw[yg] + (lz + 1) * kPP;   // corner(lxc, lyc, lz)
-                e[yg] = (uint32_t)p[0] | (uint32_t)p[kArr + kPP + kP + 1] << 8;
-            }
-#pragma unroll
-            for (int yg = 0; yg < 4; ++yg)
-                if (ok[yg]) bstore16(r, yo[yg], (e[yg] >> 5) & 0x0707u);
-        }
-    } else {
-        // planes of 2 GiB or more: one cell (two bytes) per lane, rows
-        // r = (lane >> 4) + 4 it, 64-bit addresses; the LDS reads of 8 rows
-        // are issued together (rows and cells outside the boxes read clamped in-image
-        // bytes and store nothing)
-        const int lx = (lane & 15) - 1;
-        const bool okx = lx <= wx;
-        const int lxc = okx ? lx : wx;
-        const int gx = wrap_add(gx0 + lxc, Lx);
-        const int nit = 4 * (wz + 2);               // rows with lz <= wz
-        for (int it0 = 0; it0 < nit; it0 += 8) {
-            uint32_t vc[8], vb[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int it = it0 + u;
-                const int lyc = min((lane >> 4) + 4 * (it & 3) - 1, wy), lzc = min((it >> 2) - 1, wz);
-                vc[u] = lat[(lzc + 1) * kPP + (lyc + 1) * kP + (lxc + 1)];
-                vb[u] = lat[kArr + (lzc + 2) * kPP + (lyc + 2) * kP + (lxc + 2)];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int it = it0 + u;
-                const int ly = (lane >> 4) + 4 * (it & 3) - 1, lz = (it >> 2) - 1;
-                if (!okx || ly > wy || lz > wz) continue;
-                const bool corner = lx >= 0 && ly >= 0 && lz >= 0;
-                const bool body = lx < wx && ly < wy && lz < wz;
-                if (!corner && !body) continue;
-                const int gy = wrap_add(gy0 + ly, Ly);
-                const size_t cell = ((size_t)zplane(lz) * Ly + gy) * Lx + gx;
-                if (corner && body)
-                    gstore<uint16_t>(g + 2 * cell, (uint16_t)(decode(vc[u]) | decode(vb[u]) << 8));
-                else if (corner)
-                    gstore<uint8_t>(g + 2 * cell, (uint8_t)decode(vc[u]));
-                else
-                    gstore<uint8_t>(g + 2 * cell + 1, (uint8_t)decode(vb[u]));
-            }
-        }
-    }
+    bcc_write_back<WavePitch, SLAB, 1>(B, lat, lane, 0);
 
     // ---- wavefront reduction of the energy change and accepted count ----
     uint64_t sum = (uint64_t)dEsum;
@@ -922,18 +573,26 @@ static hipError_t launch_bcc(const DevLattice* d_lat, const WorkItem* d_items, i
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t,
-                              int colour, int kmax, int smax, hipStream_t stream, bool slab, int wpg)
+// Colour launches of at most this many blocks give a block four waves
+// (kernels_split.hip): the workgroups of 768 blocks are resident at once
+// (42 KB of LDS each, three to a CU).  us per launch, K = 5, S = 3, one wave
+// per block against four: 27 blocks 42.0 and 19.5, 216 42.5 and 20.0, 512
+// 43.1 and 27.2, 729 44.4 and 35.1, 1,000 (a second generation) 44.6 and
+// 44.6, 1,728 51.2 and 68.4; K = 8, S = 3: 729 54.6 and 49.0, 1,000 54.8 and
+// 64.9; K = 2, S = 1: 729 35.0 and 24.9, 1,728 40.9 and 43.8.
+constexpr int kSplitBlocks = 768;
+
+hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int n_blocks,
+                              int t, int colour, int kmax, int smax, hipStream_t stream, bool slab, int wpg)
 {
     if (n_groups <= 0) return hipSuccess;
     if (lattice == 1)
         return slab ? hipErrorInvalidValue
                     : launch_sweep_phase_fcc(d_lat, d_items, n_groups, t, colour, smax, stream,
                                              wpg ? wpg : kWavesPerGroupFcc);
-    if (slab) return wpg && wpg != kWavesPerGroup ? hipErrorInvalidValue
-                                                   : launch_bcc<true, kWavesPerGroup>(d_lat, d_items, n_groups, t,
-                                                                                     colour, kmax, smax, stream);
     if (wpg && wpg != kWavesPerGroup) return hipErrorInvalidValue;
+    if (n_blocks <= kSplitBlocks) return launch_sweep_split(d_lat, d_items, n_groups, t, colour, kmax, smax, stream, slab);
+    if (slab) return launch_bcc<true, kWavesPerGroup>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
     return launch_bcc<false, kWavesPerGroup>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
 }
 

@@ -133,8 +133,8 @@ extern "C" smcx_status smcx_sweep_noalloc(const smcx_desc* desc, uint8_t* d_spec
     const int groups = (h.blocks_per_colour + wpg - 1) / wpg;
     for (int32_t k = 0; k < n; ++k)
         for (int col = 0; col < 8; ++col) {
-            st = hip_ok(launch_sweep_phase(lattice, (const DevLattice*)(d + kOffLat), nullptr, groups, k, col, kmax,
-                                           S, stream),
+            st = hip_ok(launch_sweep_phase(lattice, (const DevLattice*)(d + kOffLat), nullptr, groups, h.blocks_per_colour, k,
+                                           col, kmax, S, stream),
                         "sweep_phase launch");
             if (st) return st;
         }

@@ -342,7 +342,8 @@ smcx_status smcx_server_step(smcx_server* s, int32_t* n_resident, int32_t* n_wai
             return steps_of(x) > steps_of(y);
         });
         s->h_items.clear();
-        struct Group { int lattice, kmax, smax; size_t begin; std::vector<std::pair<int, size_t>> ends; };
+        struct End { int steps; size_t item; int blocks; };   // steps, items and blocks up to a request
+        struct Group { int lattice, kmax, smax; size_t begin; std::vector<End> ends; };
         std::vector<Group> groups;
         for (Request* q : run) {
             if (groups.empty() || groups.back().lattice != q->desc.lattice || groups.back().kmax != q->kmax ||
@@ -350,7 +351,8 @@ smcx_status smcx_server_step(smcx_server* s, int32_t* n_resident, int32_t* n_wai
                 groups.push_back(Group{q->desc.lattice, q->kmax, q->smax, s->h_items.size(), {}});
             for (int g = 0; g < q->groups; ++g)
                 s->h_items.push_back(WorkItem{q->slot, g * waves_per_group(q->desc.lattice)});
-            groups.back().ends.push_back({steps_of(q), s->h_items.size()});
+            const int before = groups.back().ends.empty() ? 0 : groups.back().ends.back().blocks;
+            groups.back().ends.push_back({steps_of(q), s->h_items.size(), before + q->lat.blocks_per_colour});
         }
         if (s->h_items.size() > s->items_cap) {
             // grows rarely (the work list of a larger mix): the previous
@@ -370,15 +372,19 @@ smcx_status smcx_server_step(smcx_server* s, int32_t* n_resident, int32_t* n_wai
                                               hipMemcpyHostToDevice, s->stream), "hipMemcpyAsync(items)");
         if (st) return st;
         for (const Group& G : groups) {
-            const int tmax = G.ends.front().first;
+            const int tmax = G.ends.front().steps;
             for (int t = 0; t < tmax; ++t) {
                 // requests with more than t steps this round form a prefix
                 size_t end = G.begin;
-                for (const auto& e : G.ends)
-                    if (e.first > t) end = e.second;
+                int blocks = 0;
+                for (const End& e : G.ends)
+                    if (e.steps > t) {
+                        end = e.item;
+                        blocks = e.blocks;
+                    }
                 for (int c = 0; c < 8; ++c) {
                     hipError_t e = launch_sweep_phase(G.lattice, s->d_lats, s->d_items + G.begin, (int)(end - G.begin),
-                                                      t, c, G.kmax, G.smax, s->stream);
+                                                      blocks, t, c, G.kmax, G.smax, s->stream);
                     if (e != hipSuccess) return shipc(s, e, "sweep_phase launch");
                 }
             }

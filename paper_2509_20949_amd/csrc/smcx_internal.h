@@ -165,9 +165,14 @@ int build_wtab(const int32_t* epi, int K, int S, int kmax, int smax, int bias, b
 // wpg: blocks per workgroup, 0 for the lattice type's default
 // (waves_per_group); single FCC lattices may take kWavesPerGroupFccWide
 // (plan_waves_per_group).
-hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups,
+// n_blocks: the blocks the n_groups groups hold between them (it chooses the
+// kernel, never the result).
+hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int n_blocks,
                               int t, int colour, int kmax, int smax, hipStream_t stream, bool slab = false,
                               int wpg = 0);
+// The BCC colour launch with four waves per block (kernels_split.hip).
+hipError_t launch_sweep_split(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t, int colour, int kmax,
+                              int smax, hipStream_t stream, bool slab);
 hipError_t launch_pair_counts(int lattice, const uint8_t* species, const int32_t L[3], int K, int S,
                               unsigned long long* d_counts, hipStream_t stream);
 hipError_t launch_sweep_phase_fcc(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t,
