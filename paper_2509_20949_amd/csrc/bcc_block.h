@@ -43,15 +43,6 @@ using WavePitch = BccPitch<kP, kPP, kArr>;
 // bound it: one aligned word per row once the two loads are joined).
 constexpr int kStageBatch = 16;
 
-// Weight planes of the BCC kernel: row (a, b) at position a*KMAX + b of a
-// 64-entry plane, so that the position of any two 3-bit codes (a lane
-// without a site may decode a stale halo byte) stays inside its plane.  The
-// KMAX^2 rows of real species then lie in distinct LDS banks (positions
-// 8a + b, one multiply fewer, put species 4 and 0 of K = 5 on the same
-// banks: 16 % of the LDS cycles went to those conflicts).
-constexpr int kPlane = 64;
-static_assert(7 * kMaxK + 7 < kPlane, "weight plane too narrow");
-
 // Geometry of one block of colour `colour` in sweep s (wave-uniform).
 struct BccBlock {
     int Lx, Ly, Lz;

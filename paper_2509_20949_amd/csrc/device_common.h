@@ -53,6 +53,15 @@ template <bool NEG> __device__ __forceinline__ void count1(uint32_t& h, uint32_t
 constexpr int wplane(int kmax) { return ((kmax * kmax + 31) / 32) * 32; }
 constexpr int wplanes(int kmax, int smax) { return wrow_entries(kmax, smax); }
 
+// Weight planes of the BCC kernels and of the trials four lanes share: row (a, b) at position a*KMAX + b of a
+// 64-entry plane, so that the position of any two 3-bit codes (a lane
+// without a site may decode a stale halo byte) stays inside its plane.  The
+// KMAX^2 rows of real species then lie in distinct LDS banks (positions
+// 8a + b, one multiply fewer, put species 4 and 0 of K = 5 on the same
+// banks: 16 % of the LDS cycles went to those conflicts).
+constexpr int kPlane = 64;
+static_assert(7 * kMaxK + 7 < kPlane, "weight plane too narrow");
+
 // Fill the LDS planes (PS dwords apart, PS >= KMAX*KMAX) from the
 // row-major table of wrow(KMAX, SMAX) ints per row.
 template <int KMAX, int SMAX, int PS = wplane(KMAX)>

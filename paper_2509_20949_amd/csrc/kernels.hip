@@ -581,17 +581,27 @@ static hipError_t launch_bcc(const DevLattice* d_lat, const WorkItem* d_items, i
 // 44.6, 1,728 51.2 and 68.4; K = 8, S = 3: 729 54.6 and 49.0, 1,000 54.8 and
 // 64.9; K = 2, S = 1: 729 35.0 and 24.9, 1,728 40.9 and 43.8.
 constexpr int kSplitBlocks = 768;
+// FCC (37 KB of LDS, four workgroups to a CU; kernels_fcc_split.hip), us per
+// launch at K = 5, S = 3, one wave per block against four: 1 block 113 and
+// 41, 216 116 and 43, 512 117 and 59, 1,000 135 and 97, 1,331 (a second
+// generation) 136 and 136, 1,728 138 and 156; K = 3, S = 1: 1,000 94 and 59.
+constexpr int kSplitBlocksFcc = 1024;
 
 hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int n_blocks,
                               int t, int colour, int kmax, int smax, hipStream_t stream, bool slab, int wpg)
 {
     if (n_groups <= 0) return hipSuccess;
+    if (lattice == 1 && !slab && n_blocks <= kSplitBlocksFcc)
+        return launch_sweep_split_fcc(d_lat, d_items, d_items ? n_groups * kWavesPerGroupFcc : n_blocks, t, colour, smax,
+                                      stream);
     if (lattice == 1)
         return slab ? hipErrorInvalidValue
                     : launch_sweep_phase_fcc(d_lat, d_items, n_groups, t, colour, smax, stream,
                                              wpg ? wpg : kWavesPerGroupFcc);
     if (wpg && wpg != kWavesPerGroup) return hipErrorInvalidValue;
-    if (n_blocks <= kSplitBlocks) return launch_sweep_split(d_lat, d_items, n_groups, t, colour, kmax, smax, stream, slab);
+    if (n_blocks <= kSplitBlocks)
+        return launch_sweep_split(d_lat, d_items, d_items ? n_groups * kWavesPerGroup : n_blocks, t, colour, kmax, smax,
+                                  stream, slab);
     if (slab) return launch_bcc<true, kWavesPerGroup>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
     return launch_bcc<false, kWavesPerGroup>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
 }

@@ -34,18 +34,12 @@
 #include <type_traits>
 
 #include "bcc_block.h"
+#include "split_trial.h"
 
 namespace smcx {
 
 namespace split {
 
-// quad_perm controls: lanes 0..3 of every quad take the named lanes' values
-constexpr int kSwap = 1 | 0 << 2 | 3 << 4 | 2 << 6;     // the other lane of the pair
-constexpr int kSwap2 = 2 | 3 << 2 | 0 << 4 | 1 << 6;    // the other pair of the quad
-template <int CTRL> __device__ __forceinline__ uint32_t quad(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
-}
 // LDS layout of the block image: with the lane map below, a byte read of a
 // wave takes 2.9 LDS cycles on average over the sublattices, directions and
 // offsets of a trial (a bank model; 4.3 with the one-wave kernel's pitches).
@@ -57,9 +51,7 @@ constexpr int kS1[2] = {Pitch::ARR, -Pitch::kBodyFromCorner};
 
 // What a lane's place in its trial fixes for the whole launch.
 struct LanePart {
-    int at_partner;      // 1 on lanes that count the partner's neighbourhood
-    uint32_t lead;       // all ones on the trial's lead lane (it adds the constant terms)
-    uint32_t bias;       // the histogram fields' offset, on the lead lane
+    LaneRole role;
     int s1[2];           // first-shell base from the lane's centre, by the trial's sublattice
     int z, x, y;         // bases of the lane's z plane, x column and y neighbour, from its centre
 };
@@ -67,74 +59,20 @@ struct LanePart {
 template <int KMAX, bool DOT> __device__ __forceinline__ LanePart lane_part(int lane)
 {
     LanePart c;
-    const bool pj = lane & 1, hf = lane & 2;
-    c.at_partner = pj ? 1 : 0;
-    c.lead = (lane & 3) == 0 ? ~0u : 0u;
-    c.bias = c.lead & (DOT ? 0x20202020u
-                     : Field<KMAX>::F == 5 ? 0x10u * (1u | 1u << 5 | 1u << 10 | 1u << 15 | 1u << 20 | 1u << 25) : 0u);
-    c.s1[0] = (pj ? kS1[1] : kS1[0]) + (hf ? kZ : 0);
-    c.s1[1] = (pj ? kS1[0] : kS1[1]) + (hf ? kZ : 0);
-    c.z = (hf ? kZ : -kZ) - kY;    // (each less kY: their offsets 0 .. 2 kY are then immediates)
-    c.x = (hf ? kX : -kX) - kY;
-    c.y = hf ? kY : -kY;
+    c.role = lane_role(lane, DOT ? 0x20202020u
+                           : Field<KMAX>::F == 5 ? 0x10u * (1u | 1u << 5 | 1u << 10 | 1u << 15 | 1u << 20 | 1u << 25) : 0u);
+    const int up = c.role.half > 0 ? kZ : 0;
+    c.s1[0] = kS1[c.role.at_partner] + up;
+    c.s1[1] = kS1[1 - c.role.at_partner] + up;
+    c.z = c.role.half * kZ - kY;   // (each less kY: their offsets 0 .. 2 kY are then immediates)
+    c.x = c.role.half * kX - kY;
+    c.y = c.role.half * kY;
     return c;
 }
 
-// acc + sum over shells and fields of field(s, p) * w[s*KMAX + p], modulo
-// 2^32 (the fields of one lane's partial counts).
-template <int KMAX, int SMAX, int NF>
-__device__ __forceinline__ uint32_t weigh_fields(const uint32_t (&h)[kMaxS], const int32_t* w, uint32_t acc)
-{
-    constexpr int F = Field<KMAX>::F;
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s)
-#pragma unroll
-        for (int p = 0; p < NF; ++p)
-            acc = mad24((h[s] >> (F * p)) & ((1u << F) - 1u), w[(s * KMAX + p) * kPlane], acc);
-    return acc;
-}
-
-// bias + sum of 1 << code over N codes, one shift-add each.  One asm block:
-// between blocks of one chain the compiler puts a wait state, which here,
-// one wave to a SIMD, costs an issue slot.
-template <int N> __device__ __forceinline__ uint32_t count_all(uint32_t bias, const uint32_t (&c)[N])
-{
-    static_assert(N == 3 || N == 4 || N == 6, "neighbours of a lane per shell");
-    uint32_t h;
-    if constexpr (N == 3)
-        asm("v_lshl_add_u32 %0, 1, %1, %4\n\tv_lshl_add_u32 %0, 1, %2, %0\n\tv_lshl_add_u32 %0, 1, %3, %0"
-            : "=&v"(h) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(bias));
-    else if constexpr (N == 4)
-        asm("v_lshl_add_u32 %0, 1, %1, %5\n\tv_lshl_add_u32 %0, 1, %2, %0\n\tv_lshl_add_u32 %0, 1, %3, %0\n\t"
-            "v_lshl_add_u32 %0, 1, %4, %0"
-            : "=&v"(h) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(bias));
-    else
-        asm("v_lshl_add_u32 %0, 1, %1, %7\n\tv_lshl_add_u32 %0, 1, %2, %0\n\tv_lshl_add_u32 %0, 1, %3, %0\n\t"
-            "v_lshl_add_u32 %0, 1, %4, %0\n\tv_lshl_add_u32 %0, 1, %5, %0\n\tv_lshl_add_u32 %0, 1, %6, %0"
-            : "=&v"(h) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(c[4]), "v"(c[5]), "v"(bias));
-    return h;
-}
-
-// The acceptance edge of a draw (Eq. (3)): a change dE with float(dE) <= lo
-// is accepted without the threshold tables, one with float(dE) > lo + 16 is
-// rejected, in between the table decides (accept_edges, device_common.h: lo
-// is its lower edge, but never below 0, so that dE <= 0 passes; with the
-// upper edge taken as lo + 16 the band only grows or shifts by the two
-// roundings, 1 micro-eV of the 4.7 in hand).  Every edge of a draw u > 0 lies
-// below 2^24 - 16.  A trial without a site gets -inf (always rejected), u = 0
-// NaN (neither test passes: the table decides).
-__device__ __forceinline__ float accept_edge(uint32_t u, float ln2kT, bool valid)
-{
-    float elo, ehi;
-    accept_edges(u, ln2kT, elo, ehi);
-    const float lo = u == 0u ? __builtin_nanf("") : fmaxf(elo, 0.0f);
-    return valid ? lo : -__builtin_inff();
-}
-
 // One trial of sublattice SUB.  p: the lane's centre (the site or its
-// partner), lo: the draw's edge, u_at: the draw itself in LDS.
-// Every lane of the trial takes the same decision; each stores the new code
-// of its own centre.  Returns the accepted change.
+// partner), lo: the draw's edge, u_at: the draw itself in LDS.  Returns the
+// accepted change.
 // (Reading the next trial's centres ahead of this decision, with the two
 // cells it may change put right afterwards, took 3 % longer: the selects cost
 // the issue slots that the hidden LDS round trip gave.)
@@ -142,7 +80,6 @@ template <int KMAX, int SMAX, int SUB, int MODE>
 __device__ __forceinline__ int32_t trial(uint8_t* p, const LanePart& c, float lo, const uint32_t* u_at,
                                          const int32_t* wtab, const double* tab, uint32_t& nacc)
 {
-    constexpr bool DOT = MODE == kWtabDot;
     const uint32_t own = *p;
     // all neighbours before the first use
     const uint8_t *p1 = p + c.s1[SUB], *pz = p + c.z, *px = p + c.x, *py = p + c.y;
@@ -162,68 +99,16 @@ __device__ __forceinline__ int32_t trial(uint8_t* p, const LanePart& c, float lo
         n3[4] = px[0];
         n3[5] = px[2 * kY];
     }
-    const uint32_t a = own >> 5;
-    const uint32_t row4 = __umul24(a, 4u * KMAX) + quad<kSwap>(a << 2);   // row (own code, other code)
-    const int32_t* w = (const int32_t*)((const uint8_t*)wtab + row4);
-    // the byte-dot row is requested before the counting (the other forms load
-    // theirs as they go)
-    constexpr int NW = DOT ? 3 * SMAX + 1 : 1;
-    int32_t wr[NW];
-#pragma unroll
-    for (int k = 0; k < NW; ++k) wr[k] = w[(DOT ? k : SMAX * KMAX) * kPlane];
-    __builtin_amdgcn_sched_barrier(0);
-    uint32_t h[kMaxS];
-    h[0] = count_all(c.bias, n1);
-    if constexpr (SMAX >= 2) h[1] = count_all(c.bias, n2);
-    if constexpr (SMAX >= 3) h[2] = count_all(c.bias, n3);
-    const uint32_t other = quad<kSwap>(own);
-    uint32_t acc;
-    if constexpr (DOT) {
-        // the three base-256 digits of the folded weights, in chains of their own
-        int32_t A0 = (int32_t)((uint32_t)wr[3 * SMAX] & c.lead), A1 = 0, A2 = 0;
-#pragma unroll
-        for (int s = 0; s < SMAX; ++s) {
-            // (K <= 4: byte 3, where the last species' bit 31 lies, weighs nothing)
-            const int32_t d = (int32_t)(KMAX == 5 ? h[s] & 0x7fffffffu : h[s]);
-            A0 = __builtin_amdgcn_sdot4(d, wr[3 * s + 0], A0, false);
-            A1 = __builtin_amdgcn_sdot4(d, wr[3 * s + 1], A1, false);
-            A2 = __builtin_amdgcn_sdot4(d, wr[3 * s + 2], A2, false);
-        }
-        acc = ((((uint32_t)A2 << 8) + (uint32_t)A1) << 8) + (uint32_t)A0;
-    } else {
-        acc = weigh_fields<KMAX, SMAX, MODE == kWtabDrop ? KMAX - 1 : KMAX>(
-            h, w, (uint32_t)wr[0] & c.lead);
-    }
-    acc += quad<kSwap>(acc);
-    acc += quad<kSwap2>(acc);
-    const int32_t dE = (int32_t)acc;
-
-    // Metropolis decision, Eq. (3); the exact test on the FP64 byte tables
-    // only where a lane's change lies between its edges
-    const float fdE = (float)dE;
-    bool accept = fdE <= lo;
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!accept & !(fdE > lo + 16.0f)) != 0, 0)) {
-        // (the table decides as the edges do where those suffice; a lane
-        // without a site keeps its edge's answer)
-        const uint32_t u = *u_at;
-        const int x = dE < 1 ? 1 : (dE > (1 << 24) - 1 ? (1 << 24) - 1 : dE);
-        const uint8_t* tb = (const uint8_t*)tab;
-        const double thr = (gload<double>(tb + 8 * (512 + (x >> 16))) * gload<double>(tb + 8 * (256 + ((x >> 8) & 255)))) *
-                           gload<double>(tb + 8 * (x & 255));
-        accept = !(lo < 0.0f) & ((dE <= 0) | ((dE < (1 << 24)) & ((double)u < thr)));
-    }
-    nacc += (accept & (own != other)) ? 1u : 0u;
-    *p = (uint8_t)(accept ? other : own);   // (the two lanes of a centre store the same value)
-    return accept ? dE : 0;                 // (0 for equal species: their row is zero)
+    return finish_trial<KMAX, SMAX, Field<KMAX>::F, MODE>(p, own, n1, n2, n3, c.role, lo, u_at, wtab, tab, nacc);
 }
 
 }  // namespace split
 
-// One block per workgroup of 4 waves; n_groups counts the groups of
-// kWavesPerGroup blocks (work items) of the launch, as for sweep_phase_kernel.
+// One block per workgroup of 4 waves; n workgroups: the blocks of a single
+// lattice, or kWavesPerGroup per work item.
 template <int KMAX, int SMAX, bool SLAB>
 __global__ __launch_bounds__(4 * kWave)
-void sweep_split_kernel(const DevLattice* __restrict__ lats, const WorkItem* __restrict__ items, int n_groups, int t,
+void sweep_split_kernel(const DevLattice* __restrict__ lats, const WorkItem* __restrict__ items, int n, int t,
                         int colour)
 {
     using split::Pitch;
@@ -240,7 +125,7 @@ void sweep_split_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
 
     const int wave = wave_id();
     const int lane = threadIdx.x % kWave;
-    const int grp = xcd_group(n_groups * kWavesPerGroup);
+    const int grp = xcd_group(n);
     if (grp < 0) return;
     int li = 0, f = grp;
     if (items) {
@@ -328,9 +213,9 @@ void sweep_split_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
                     const int q = 2 * (9 * rz + 3 * ry + rx);
                     const float2 lo = *(const float2*)(edges + word + 128 * rx);
                     const uint32_t* u = draws + word + 128 * rx;
-                    uint8_t* p0 = at + rx + __mul24(__builtin_amdgcn_readlane(partner_off, q), part.at_partner);
+                    uint8_t* p0 = at + rx + __mul24(__builtin_amdgcn_readlane(partner_off, q), part.role.at_partner);
                     uint8_t* p1 = at + rx + Pitch::kBodyFromCorner +
-                                  __mul24(__builtin_amdgcn_readlane(partner_off, q + 1), part.at_partner);
+                                  __mul24(__builtin_amdgcn_readlane(partner_off, q + 1), part.role.at_partner);
                     int32_t d = split::trial<KMAX, SMAX, 0, MODE>(p0, part, lo.x, u, s_w, g_tab, nacc);
                     __builtin_amdgcn_wave_barrier();
                     d += split::trial<KMAX, SMAX, 1, MODE>(p1, part, lo.y, u + 1, s_w, g_tab, nacc);
@@ -372,42 +257,39 @@ void sweep_split_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
 }
 
 template <int KMAX, bool SLAB>
-static hipError_t launch_s(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t, int colour, int smax,
+static hipError_t launch_s(const DevLattice* d_lat, const WorkItem* d_items, int n, int t, int colour, int smax,
                            hipStream_t stream)
 {
-    const dim3 grid(xcd_grid(n_groups * kWavesPerGroup)), block(4 * kWave);
+    const dim3 grid(xcd_grid(n)), block(4 * kWave);
     switch (smax) {
-    case 1: hipLaunchKernelGGL((sweep_split_kernel<KMAX, 1, SLAB>), grid, block, 0, stream, d_lat, d_items, n_groups, t,
-                               colour); break;
-    case 2: hipLaunchKernelGGL((sweep_split_kernel<KMAX, 2, SLAB>), grid, block, 0, stream, d_lat, d_items, n_groups, t,
-                               colour); break;
-    case 3: hipLaunchKernelGGL((sweep_split_kernel<KMAX, 3, SLAB>), grid, block, 0, stream, d_lat, d_items, n_groups, t,
-                               colour); break;
+    case 1: hipLaunchKernelGGL((sweep_split_kernel<KMAX, 1, SLAB>), grid, block, 0, stream, d_lat, d_items, n, t, colour); break;
+    case 2: hipLaunchKernelGGL((sweep_split_kernel<KMAX, 2, SLAB>), grid, block, 0, stream, d_lat, d_items, n, t, colour); break;
+    case 3: hipLaunchKernelGGL((sweep_split_kernel<KMAX, 3, SLAB>), grid, block, 0, stream, d_lat, d_items, n, t, colour); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 template <bool SLAB>
-static hipError_t launch_k(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t, int colour, int kmax,
+static hipError_t launch_k(const DevLattice* d_lat, const WorkItem* d_items, int n, int t, int colour, int kmax,
                            int smax, hipStream_t stream)
 {
     switch (kmax) {
-    case 2: return launch_s<2, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 3: return launch_s<3, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 4: return launch_s<4, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 5: return launch_s<5, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 6: return launch_s<6, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 8: return launch_s<8, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 2: return launch_s<2, SLAB>(d_lat, d_items, n, t, colour, smax, stream);
+    case 3: return launch_s<3, SLAB>(d_lat, d_items, n, t, colour, smax, stream);
+    case 4: return launch_s<4, SLAB>(d_lat, d_items, n, t, colour, smax, stream);
+    case 5: return launch_s<5, SLAB>(d_lat, d_items, n, t, colour, smax, stream);
+    case 6: return launch_s<6, SLAB>(d_lat, d_items, n, t, colour, smax, stream);
+    case 8: return launch_s<8, SLAB>(d_lat, d_items, n, t, colour, smax, stream);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_sweep_split(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t, int colour, int kmax,
+hipError_t launch_sweep_split(const DevLattice* d_lat, const WorkItem* d_items, int n, int t, int colour, int kmax,
                               int smax, hipStream_t stream, bool slab)
 {
-    return slab ? launch_k<true>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream)
-                : launch_k<false>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
+    return slab ? launch_k<true>(d_lat, d_items, n, t, colour, kmax, smax, stream)
+                : launch_k<false>(d_lat, d_items, n, t, colour, kmax, smax, stream);
 }
 
 }  // namespace smcx

@@ -170,9 +170,13 @@ int build_wtab(const int32_t* epi, int K, int S, int kmax, int smax, int bias, b
 hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int n_blocks,
                               int t, int colour, int kmax, int smax, hipStream_t stream, bool slab = false,
                               int wpg = 0);
-// The BCC colour launch with four waves per block (kernels_split.hip).
-hipError_t launch_sweep_split(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t, int colour, int kmax,
+// The colour launch with four waves per block (kernels_split.hip,
+// kernels_fcc_split.hip): n workgroups, one per block of a single lattice or
+// waves_per_group(lattice) per work item.
+hipError_t launch_sweep_split(const DevLattice* d_lat, const WorkItem* d_items, int n, int t, int colour, int kmax,
                               int smax, hipStream_t stream, bool slab);
+hipError_t launch_sweep_split_fcc(const DevLattice* d_lat, const WorkItem* d_items, int n, int t, int colour, int smax,
+                                  hipStream_t stream);
 hipError_t launch_pair_counts(int lattice, const uint8_t* species, const int32_t L[3], int K, int S,
                               unsigned long long* d_counts, hipStream_t stream);
 hipError_t launch_sweep_phase_fcc(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t,

@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
 # 768; widths 12 (whole rounds), 2 (the narrowest) and 5..6 (partial lanes)
 FEW = dict(L=(144, 48, 113), block=(12, 2, 6), blocks=720)
 MANY = dict(L=(144, 48, 125), block=(12, 2, 6), blocks=792)
+# FCC: 6 * 12 * 14 = 1008 and 6 * 12 * 15 = 1080 around 1024
+FCC_FEW = dict(L=(144, 48, 161), block=(12, 2, 6), blocks=1008)
+FCC_MANY = dict(L=(144, 48, 173), block=(12, 2, 6), blocks=1080)
 
 
 def note(msg):
@@ -74,6 +77,19 @@ def test_bcc_full_rows_around_the_rule(smcx, orc, shape, K):
     epi = np.triu(v) + np.transpose(np.triu(v, 1), (0, 2, 1))
     run(smcx, orc, shape, epi, 5000.0, 40 + K)
     run(smcx, orc, shape, epi, 1.0, 50 + K, n_sweeps=1)
+
+
+@pytest.mark.parametrize("shape", [FCC_FEW, FCC_MANY], ids=["few", "many"])
+@pytest.mark.parametrize("K,S", [(2, 1), (3, 2), (4, 3), (5, 3)])
+def test_fcc_kernels_around_the_rule(smcx, orc, shape, K, S):
+    run(smcx, orc, shape, W.epi_table(S, K, 25.0, np.random.default_rng(K + 10 * S)), 900.0, 400 + K, lattice=1)
+
+
+@pytest.mark.parametrize("shape", [FCC_FEW, FCC_MANY], ids=["few", "many"])
+def test_fcc_full_rows_around_the_rule(smcx, orc, shape):
+    v = np.random.default_rng(5).choice([-(1 << 22) + 1, (1 << 22) - 1, 0, 123456], size=(3, 5, 5)).astype(np.int32)
+    epi = np.triu(v) + np.transpose(np.triu(v, 1), (0, 2, 1))
+    run(smcx, orc, shape, epi, 5000.0, 45, n_sweeps=1, lattice=1)
 
 
 @pytest.mark.parametrize("L,B,blocks", [((48, 48, 120), (2, 2, 12), 720), ((48, 48, 144), (2, 2, 12), 864)])
