@@ -40,30 +40,6 @@ __device__ __forceinline__ constexpr int s3off(int k)
          : k == 8 ? kP + kPP : k == 9 ? kP - kPP : k == 10 ? -kP + kPP : -kP - kPP;
 }
 
-// Counts of the second and third shells of the site at LDS byte a (its own
-// sublattice), added to h[1] and h[2]; the codes of the 6 second and 12
-// third neighbours are returned in r2 and r3 (index k: offsets s2off(k),
-// s3off(k)).
-template <int SMAX, bool NEG>
-__device__ __forceinline__ void count_outer(const uint8_t* lat, int a, uint32_t (&h)[kMaxS], uint32_t (&r2)[6],
-                                            uint32_t (&r3)[12])
-{
-    if constexpr (SMAX >= 2) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            r2[k] = lat[a + s2off(k)];
-            count1<NEG>(h[1], r2[k]);
-        }
-    }
-    if constexpr (SMAX >= 3) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            r3[k] = lat[a + s3off(k)];
-            count1<NEG>(h[2], r3[k]);
-        }
-    }
-}
-
 // First-shell offset (from the site) of neighbour e = ex + 2 ey + 4 ez.
 template <int SUB> __device__ __forceinline__ constexpr int s1off(int e)
 {
@@ -97,276 +73,358 @@ __device__ __forceinline__ uint32_t weigh(const uint32_t (&hi)[kMaxS], const uin
     return acc;
 }
 
-// The partner part of a three-shell trial for the direction E (a
-// compile-time value; the trial switches on its wave-uniform direction):
-// half of the partner's neighbourhood is cells the site's own counts
-// already hold.  In half-cell units j = i + s, s_a = +-1 the signs of E.
-// j's first shell is i + (0 or 2 s_a per axis): i, the site's second
-// neighbours i + 2 s_a along the three axes, its third neighbours in the
-// three planes with the same signs, and the far cell i + 2 s (loaded).  j's
-// second and third shells hold the site's first-shell cells k with one or
-// two direction bits flipped (popcount(k ^ E) = 1 or 2) and 3 and 9 cells
-// beyond (loaded).  With T0, T1 the site's first-shell counts over indices
-// of even and odd popcount, those two sets are T[par E ^ 1] less cell
-// E ^ 7 and T[par E] less cell E (the partner).  Sets cj (the partner's
-// code) and adds j's counts to h (+1 per neighbour, or -1 with NEG).
-template <int SUB, int E, bool NEG>
-__device__ __forceinline__ void partner3(const uint8_t* lat, int ai, const uint32_t (&s1)[8], uint32_t ci,
-                                         const uint32_t (&r2)[6], const uint32_t (&r3)[12], uint32_t T0,
-                                         uint32_t T1, uint32_t& cj, uint32_t (&h)[kMaxS])
+// The codes of the cells around a lane's trials that the lane carries from
+// one trial to the next along an x row of residue classes: corner(x), body(x),
+// corner(x + 1), .. (three-shell trials).  Around the corner site (x, y, z):
+//   a[e]   body(x - 1 + ex, y - 1 + ey, z - 1 + ez): the corner's first shell
+//   c[e]   corner(x - 1 + ex, y + ey, z + ez) before the corner trial (its
+//          own code is c[1]); corner(x + ex, ..), the body's first shell, after
+//   xc     corner(x - 1, y - 1, z), (x, y - 1, z), (x - 1, y, z - 1),
+//          (x, y, z - 1) before the corner trial; one cell on in x after it
+//   xb     body(x - 1, y + 1, z), (x, y + 1, z), (x - 1, y, z + 1),
+//          (x, y, z + 1) before the body trial; one cell on in x after it
+// A trial finds its site, its partner, its first shell and 10 of its 18
+// second and third neighbours here, and loads the cells that enter the window.
+// Each trial puts its own changes into the window; no other lane changes a
+// cell of it within the x row: in units of a/2, trials of one round are 6
+// apart and change cells within 1, the window reaches 4 ahead of the row's
+// first site and 3 behind, on the axes and sides where it holds cells.
+struct Window {
+    uint32_t a[8], c[8], xb[4], xc[4];
+};
+
+// The code of the cell (I, J, K) from the site's cell in the other
+// sublattice: from the window where it holds the cell, else loaded.
+template <int SUB, int I, int J, int K>
+__device__ __forceinline__ uint32_t other_cell(const uint8_t* lat, int ai, const Window& w)
 {
-    constexpr int ex = E & 1, ey = (E >> 1) & 1, ez = (E >> 2) & 1;
-    constexpr int dx = ex ? 1 : -1, dy = ey ? kP : -kP, dz = ez ? kPP : -kPP;
-    constexpr bool odd = (ex + ey + ez) & 1;
-    const int aj = ai + s1off<SUB>(E);
-    cj = s1[E];
-    uint32_t t_same = odd ? T1 : T0, t_other = odd ? T0 : T1;
-    count1<true>(t_same, s1[E]);        // j's third-shell cells among the site's first shell
-    count1<true>(t_other, s1[E ^ 7]);   // j's second-shell cells among them
-    // j's first shell
-    count1<NEG>(h[0], ci);
-    count1<NEG>(h[0], r2[ex ? 0 : 1]);
-    count1<NEG>(h[0], r2[ey ? 2 : 3]);
-    count1<NEG>(h[0], r2[ez ? 4 : 5]);
-    count1<NEG>(h[0], r3[(ex ? 0 : 2) + (ey ? 0 : 1)]);
-    count1<NEG>(h[0], r3[4 + (ex ? 0 : 2) + (ez ? 0 : 1)]);
-    count1<NEG>(h[0], r3[8 + (ey ? 0 : 2) + (ez ? 0 : 1)]);
-    count1<NEG>(h[0], lat[ai + dx + dy + dz]);
-    // j's second and third shells
-    h[1] = NEG ? h[1] - t_other : h[1] + t_other;
-    h[2] = NEG ? h[2] - t_same : h[2] + t_same;
-    count1<NEG>(h[1], lat[aj + dx]);
-    count1<NEG>(h[1], lat[aj + dy]);
-    count1<NEG>(h[1], lat[aj + dz]);
-    count1<NEG>(h[2], lat[aj + dx + dy]);
-    count1<NEG>(h[2], lat[aj + dx - dy]);
-    count1<NEG>(h[2], lat[aj - dx + dy]);
-    count1<NEG>(h[2], lat[aj + dx + dz]);
-    count1<NEG>(h[2], lat[aj + dx - dz]);
-    count1<NEG>(h[2], lat[aj - dx + dz]);
-    count1<NEG>(h[2], lat[aj + dy + dz]);
-    count1<NEG>(h[2], lat[aj + dy - dz]);
-    count1<NEG>(h[2], lat[aj - dy + dz]);
+    constexpr int kCell = (SUB == 0 ? 1 : -1) * WavePitch::kBodyFromCorner + I + J * kP + K * kPP;
+    if constexpr (SUB == 0 && (I == -1 || I == 0) && J == 1 && K == 0) return w.xb[I + 1];
+    else if constexpr (SUB == 0 && (I == -1 || I == 0) && J == 0 && K == 1) return w.xb[I + 3];
+    else if constexpr (SUB == 1 && (I == 0 || I == 1) && J == -1 && K == 0) return w.xc[I];
+    else if constexpr (SUB == 1 && (I == 0 || I == 1) && J == 0 && K == -1) return w.xc[I + 2];
+    else return lat[ai + kCell];
 }
 
-// Codes a trial hands to the next one (registers), so that the next trial
-// reads neither its own site, nor its partner, nor 7 of its 8 first
-// neighbours from LDS.  The next site is the other sublattice's site of the
-// lane's cell: after a corner trial at corner(x, y, z) the body trial at
-// body(x, y, z), whose first shell is corner(x + ex, y + ey, z + ez); after a
-// body trial at body(x, y, z) the corner trial of the next residue class
-// when that is corner(x + 1, y, z), whose first shell is body(x + ex,
-// y - 1 + ey, z - 1 + ez).  Of these 8 cells one is the trial's own site
-// (its new code), 6 are second or third neighbours of it that the trial
-// reads, and one more cell of its sublattice it loads for the next trial
-// (corner(x + 1, y + 1, z + 1), or body(x + 1, y - 1, z - 1)).  Nothing in
-// the trial's round changes those 7 (only sites of its residue class and
-// their partners, of the other sublattice, change).  The next site itself
-// is a first neighbour of the trial's site: only this lane's trial can have
-// swapped it.  Between the two trials no other lane changes any of these
-// cells (a lane's cells lie within one cell of its own sites, lanes are
-// three cells apart).
-struct Carry {
-    uint32_t s1[8];   // first-shell codes of the next site, index e = ex + 2 ey + 4 ez
-    uint32_t own;     // code of the next site
+// The Metropolis test of Eq. (3) for the draw u as two edges on float(dE):
+// dE <= lo is accepted and dE > hi rejected without the tables.  From e as in
+// accept_edges (device_common.h): hi = e + 8; lo = e - 8, but at least 0, so
+// that dE <= 0 passes, and at most the lower edge of u = 1, which u = 0 (e =
+// +inf, its upper edge too) passes as well.
+struct Edges {
+    float lo, hi;
 };
-// One trial: site at LDS byte ai (sublattice SUB) with its 32-bit
-// acceptance draw u.  The partner is first-shell neighbour e = ex + 2 ey +
-// 4 ez, the direction shared by the whole round (wave-uniform).  CIN: the
-// site's code and its first shell come from the previous trial (cy);
-// otherwise they are loaded.  COUT: cy is set for the next trial.
-// Adds the accepted energy change to the lane's dEsum and the wave's
-// accepted count to nacc (the same in every lane); updates the LDS image in
-// place.
-// E >= 0: the direction as a compile-time value (three shells), else e_rt.
-template <int KMAX, int SMAX, int SUB, int MODE, bool CIN, bool COUT, int E>
-__device__ __forceinline__ void trial_dir(uint8_t* lat, int ai, uint32_t u, int e_rt, bool valid,
-                                          const int32_t* wtab, const double* tab, float ln2kT, int64_t& dEsum,
-                                          uint32_t& nacc, Carry& cy)
+__device__ __forceinline__ Edges edges_of(uint32_t u, float ln2kT)
 {
-    static_assert(SMAX < 3 || E >= 0, "three-shell trials take a compile-time direction");
-    const int e = E >= 0 ? E : e_rt;
-    constexpr int F = Field<KMAX>::F;
-    constexpr bool DOT = MODE == kWtabDot;
-    // 5-bit fields (and the byte-dot form) hold bias + n_i - n_j without
-    // borrows: one packed difference per shell.  4-bit fields (KMAX = 8)
-    // count the two neighbourhoods apart.
-    constexpr bool DIFF = DOT || F == 5;
-    const uint32_t u_acc = u;
-    float elo, ehi;
-    accept_edges(u_acc, ln2kT, elo, ehi);   // depends on the draw only: off the critical path
-    const int aj = ai + s1base<SUB>() + (e & 1) + ((e >> 1) & 1) * kP + ((e >> 2) & 1) * kPP;
+    Edges x;
+    accept_edges(u, ln2kT, x.lo, x.hi);
+    x.lo = __builtin_amdgcn_fmed3f(x.lo, 0.0f, 32.0f * ln2kT - kAcceptMargin);
+    return x;
+}
 
-    // the site, its first shell, and the partner (first-shell cell e)
-    uint32_t s1[8];
-    uint32_t ci;
-    if constexpr (CIN) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s1[e] = cy.s1[e];
-        ci = cy.own;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s1[e] = lat[ai + s1off<SUB>(e)];
-        ci = lat[ai];
+// The lanes (a mask) whose trial accepts dE: the exact test on the FP64 byte
+// tables (global memory, L2-resident) only where a lane with a site lies
+// between its edges, a few percent of the rounds.  The masks live in scalar
+// registers.
+__device__ __forceinline__ uint64_t accepted_lanes(int32_t dE, uint32_t u, const Edges& x, uint64_t valid,
+                                                   const double* tab)
+{
+    const float f = (float)dE;   // exact below 2^24; both edges of a draw u > 0 lie below 2^24
+    uint64_t sure = __builtin_amdgcn_ballot_w64(f <= x.lo) & valid;
+    const uint64_t near = __builtin_amdgcn_ballot_w64(f <= x.hi) & valid & ~sure;
+    if (__builtin_expect(near != 0, 0)) {
+        const int e = dE < 1 ? 1 : (dE > (1 << 24) - 1 ? (1 << 24) - 1 : dE);
+        const uint8_t* tb = (const uint8_t*)tab;
+        const double thr = (gload<double>(tb + 8 * (512 + (e >> 16))) * gload<double>(tb + 8 * (256 + ((e >> 8) & 255)))) *
+                           gload<double>(tb + 8 * (e & 255));
+        sure |= __builtin_amdgcn_ballot_w64((dE < (1 << 24)) & ((double)u < thr)) & near;
     }
-    // Species histograms of both neighbourhoods (the partner is counted in
-    // the first shell of i and i in that of j; the constant term undoes it).
-    // In the difference form j's chains subtract and are added to i's
-    // (fields then hold bias + n_i - n_j).
-    uint32_t hi[kMaxS], hj[kMaxS];
-    constexpr uint32_t bias = DOT ? 0x20202020u
-                            : F == 5 ? 0x10u * (1u | 1u << 5 | 1u << 10 | 1u << 15 | 1u << 20 | 1u << 25) : 0u;
-#pragma unroll
-    for (int s = 0; s < kMaxS; ++s) { hi[s] = bias; hj[s] = 0u; }
-    uint32_t r2[6], r3[12];
-    uint32_t cj;
-    if constexpr (SMAX < 3) {
-        // the partner by seven v_cndmask on the bits of e (held in a vector
-        // register, e's selects stay in the trial's basic block instead of
-        // becoming branches, which would keep the loads below from being
-        // issued ahead)
-        uint32_t ev = (uint32_t)e;
-        asm volatile("" : "+v"(ev));
-        const uint32_t x0 = ev & 1u ? s1[1] : s1[0], x1 = ev & 1u ? s1[3] : s1[2];
-        const uint32_t x2 = ev & 1u ? s1[5] : s1[4], x3 = ev & 1u ? s1[7] : s1[6];
-        const uint32_t y0 = ev & 2u ? x1 : x0, y1 = ev & 2u ? x3 : x2;
-        cj = ev & 4u ? y1 : y0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) count1<false>(hi[0], s1[k]);
-        count_outer<SMAX, false>(lat, ai, hi, r2, r3);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) count1<DIFF>(hj[0], lat[aj + s1off<1 - SUB>(k)]);
-        uint32_t q2[6], q3[12];
-        count_outer<SMAX, DIFF>(lat, aj, hj, q2, q3);
-    } else {
-        uint32_t T0 = 0u, T1 = 0u;   // the site's first shell, indices of even / odd popcount
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (__builtin_popcount(k) & 1) count1<false>(T1, s1[k]);
-            else count1<false>(T0, s1[k]);
-        }
-        hi[0] += T0 + T1;
-        count_outer<3, false>(lat, ai, hi, r2, r3);
-        // j's counts: subtracted from i's chains in the difference form
-        auto& hp = *(DIFF ? &hi : &hj);
-        partner3<SUB, (E >= 0 ? E : 0), DIFF>(lat, ai, s1, ci, r2, r3, T0, T1, cj, hp);
-    }
-    // Row (a, b) of the weight planes, a = ci >> 5 and b = cj >> 5, at byte
-    // 4 (a*KMAX + b) of a plane.  (Lanes without a site in this round may
-    // decode stale halo bytes: their row still lies inside the planes, and
-    // their result is discarded.)
-    const uint32_t row4 = __umul24(ci >> 5, 4u * KMAX) + ((cj >> 5) << 2);
-    const int32_t* w = (const int32_t*)((const uint8_t*)wtab + row4);
-    // the cell of this sublattice the next trial's first shell needs besides
-    // these: corner(x + 1, y + 1, z + 1) or body(x + 1, y - 1, z - 1)
-    const uint32_t fresh = COUT ? (uint32_t)lat[ai + (SUB == 0 ? 1 + kP + kPP : 1 - kP - kPP)] : 0u;
-    if constexpr (DIFF) {
-#pragma unroll
-        for (int s = 0; s < kMaxS; ++s) { hi[s] += hj[s]; hj[s] = 0u; }
-    }
+    return sure;
+}
 
-    uint32_t acc;
-    if constexpr (DOT) {
+// What a wave's trials add up.
+struct Sums {
+    int32_t dE;      // of the current class (two changes below 2^29 each)
+    uint32_t nacc;   // accepted swaps of the wave: wave-uniform, counted on the scalar unit
+};
+
+// Weigh the histograms (difference form: hi holds bias + n_i - n_j, hj is 0)
+// with the pair's row and decide: returns the accepted lanes.  row: the
+// byte-dot words, loaded ahead; w: the row in LDS for the other forms.
+template <int KMAX, int SMAX, int MODE>
+__device__ __forceinline__ int32_t energy_change(const uint32_t (&hi)[kMaxS], const uint32_t (&hj)[kMaxS],
+                                                 const int32_t (&row)[3 * kMaxS + 1], const int32_t* w)
+{
+    if constexpr (MODE == kWtabDot) {
         // bytes 32 + n_i - n_j (bit 31, the last species, masked off) dotted
         // with the three base-256 digits of the folded weights, in one
         // chain: ((A2 * 256 + A1) * 256 + constant) + A0
-        constexpr int PS = kPlane;
         int32_t d[kMaxS];
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) d[s] = (int32_t)(hi[s] & 0x7fffffffu);
         int32_t X = 0;
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], w[(3 * s + 2) * PS], X, false);
+        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], row[3 * s + 2], X, false);
         X = (int32_t)((uint32_t)X << 8);
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], w[(3 * s + 1) * PS], X, false);
-        X = (int32_t)(((uint32_t)X << 8) + (uint32_t)w[3 * SMAX * PS]);
+        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], row[3 * s + 1], X, false);
+        X = (int32_t)(((uint32_t)X << 8) + (uint32_t)row[3 * SMAX]);
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], w[(3 * s + 0) * PS], X, false);
-        acc = (uint32_t)X;
+        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], row[3 * s], X, false);
+        return X;
     } else {
         // With kWtabDrop the rows fold in the last species, whose count
         // differences follow from the others (both sites have the same
         // number of neighbours per shell): only fields 0 .. KMAX-2 are read.
-        acc = weigh<KMAX, SMAX, MODE == kWtabDrop ? KMAX - 1 : KMAX>(hi, hj, w,
-                                                                      (uint32_t)w[SMAX * KMAX * kPlane]);
-    }
-    const int32_t dE = (int32_t)acc;
-
-    // Metropolis decision, Eq. (3): the exact test on the FP64 byte tables,
-    // evaluated only when a lane's dE falls between its bounds (a
-    // wave-uniform branch, taken by a few percent of the rounds).  float(dE)
-    // is exact wherever `up` holds.
-    const float fdE = (float)dE;
-    const bool up = (dE > 0) & (dE < (1 << 24));
-    const bool sure = fdE <= elo;
-    const bool near = up & ((!sure & (fdE <= ehi)) | (u_acc == 0u));
-    bool up_ok = up & sure;
-    if (__builtin_amdgcn_ballot_w64(near)) {
-        const int e = dE < 1 ? 1 : (dE > (1 << 24) - 1 ? (1 << 24) - 1 : dE);
-        const uint8_t* tb = (const uint8_t*)tab;   // global memory (L2-resident)
-        const double thr = (gload<double>(tb + 8 * (512 + (e >> 16))) * gload<double>(tb + 8 * (256 + ((e >> 8) & 255)))) *
-                           gload<double>(tb + 8 * (e & 255));
-        up_ok = near ? (double)u_acc < thr : up_ok;
-    }
-    const bool accept = valid & (ci != cj) & ((dE <= 0) | up_ok);
-    // Both bytes are stored by every lane (unchanged unless accepted): no
-    // two lanes of a round touch the same byte, and a branch-free trial
-    // keeps the whole round in one basic block for the scheduler.
-    const uint32_t ci_new = accept ? cj : ci;
-    lat[ai] = (uint8_t)ci_new;
-    lat[aj] = (uint8_t)(accept ? ci : cj);
-    dEsum += (int64_t)(accept ? dE : 0);
-    nacc += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(accept));   // wave-uniform: counted on the scalar unit
-
-    if constexpr (COUT) {
-        // the next site is first-shell cell kNext of this site; it changed
-        // iff it was the partner of an accepted swap
-        constexpr int kNext = SUB == 0 ? 7 : 1;
-        cy.own = accept && e == kNext ? ci : s1[kNext];
-        if constexpr (SUB == 0) {   // next: body(x, y, z); its first shell corner(x + ex, y + ey, z + ez)
-            cy.s1[0] = ci_new;
-            cy.s1[1] = r2[0];   // +x
-            cy.s1[2] = r2[2];   // +y
-            cy.s1[3] = r3[0];   // +x +y
-            cy.s1[4] = r2[4];   // +z
-            cy.s1[5] = r3[4];   // +x +z
-            cy.s1[6] = r3[8];   // +y +z
-            cy.s1[7] = fresh;   // +x +y +z
-        } else {                    // next: corner(x + 1, y, z); its first shell body(x + ex, y - 1 + ey, z - 1 + ez)
-            cy.s1[0] = r3[11];  // -y -z
-            cy.s1[1] = fresh;   // +x -y -z
-            cy.s1[2] = r2[5];   // -z
-            cy.s1[3] = r3[5];   // +x -z
-            cy.s1[4] = r2[3];   // -y
-            cy.s1[5] = r3[1];   // +x -y
-            cy.s1[6] = ci_new;  // the site itself
-            cy.s1[7] = r2[0];   // +x
-        }
+        return (int32_t)weigh<KMAX, SMAX, MODE == kWtabDrop ? KMAX - 1 : KMAX>(hi, hj, w,
+                                                                               (uint32_t)w[SMAX * KMAX * kPlane]);
     }
 }
 
-// One trial with the round's direction e (wave-uniform).  Three-shell trials
-// switch on it before anything else: each case is then one straight-line
-// trial whose loads (the site's and the partner's cells) the compiler can
-// issue together.
-template <int KMAX, int SMAX, int SUB, int MODE, bool CIN, bool COUT>
-__device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, bool valid, const int32_t* wtab,
-                                      const double* tab, float ln2kT, int64_t& dEsum, uint32_t& nacc, Carry& cy)
+// Row (a, b) of the weight planes, a = ci >> 5 and b = cj >> 5, at byte
+// 4 (a*KMAX + b) of a plane.  (Lanes without a site in this round may decode
+// stale halo bytes: their row still lies inside the planes, and their result
+// is discarded.)
+template <int KMAX>
+__device__ __forceinline__ const int32_t* weight_row(const int32_t* wtab, uint32_t ci, uint32_t cj)
+{
+    const uint32_t row4 = __umul24(ci >> 5, 4u * KMAX) + ((cj >> 5) << 2);
+    return (const int32_t*)((const uint8_t*)wtab + row4);
+}
+
+template <int KMAX, bool DOT>
+constexpr uint32_t kFieldBias = DOT ? 0x20202020u
+                              : Field<KMAX>::F == 5 ? 0x10u * (1u | 1u << 5 | 1u << 10 | 1u << 15 | 1u << 20 | 1u << 25) : 0u;
+
+// One three-shell trial: the site at LDS byte ai (sublattice SUB), its partner
+// first-shell neighbour E = ex + 2 ey + 4 ez (the direction shared by the
+// round: the trial switches on it, wave-uniform, before anything else, so that
+// each case is one straight line whose loads issue together).
+//
+// Half of the partner's neighbourhood is cells the site's own counts already
+// hold.  In half-cell units j = i + s, s_a = +-1 the signs of E.  j's first
+// shell is i + (0 or 2 s_a per axis): i, the site's second neighbours i + 2 s_a
+// along the three axes, its third neighbours in the three planes with the same
+// signs, and the far cell i + 2 s.  j's second and third shells hold the
+// site's first-shell cells k with one or two direction bits flipped
+// (popcount(k ^ E) = 1 or 2) and 3 and 9 cells beyond.  With T0, T1 the site's
+// first-shell counts over indices of even and odd popcount, those two sets are
+// T[par E ^ 1] less cell E ^ 7 and T[par E] less cell E (the partner).
+template <int KMAX, int SUB, int MODE, int E>
+__device__ __forceinline__ void trial3(uint8_t* lat, int ai, uint32_t u, uint64_t valid, const int32_t* wtab,
+                                       const double* tab, float ln2kT, Sums& sums, Window& w)
+{
+    constexpr bool DOT = MODE == kWtabDot;
+    // 5-bit fields (and the byte-dot form) hold bias + n_i - n_j without
+    // borrows: one packed difference per shell.  4-bit fields (KMAX = 8)
+    // count the two neighbourhoods apart.
+    constexpr bool DIFF = DOT || Field<KMAX>::F == 5;
+    constexpr int ex = E & 1, ey = (E >> 1) & 1, ez = (E >> 2) & 1;
+    constexpr int dx = ex ? 1 : -1, dy = ey ? 1 : -1, dz = ez ? 1 : -1;
+    constexpr bool odd = (ex + ey + ez) & 1;
+    uint32_t (&s1)[8] = SUB == 0 ? w.a : w.c;
+    const uint32_t ci = SUB == 0 ? w.c[1] : w.a[7], cj = s1[E];
+
+    // ---- every load of the trial, then every count ----
+    // the site's second and third neighbours (indices as s2off, s3off) and
+    // the cell that completes the next trial's first shell
+    uint32_t r2[6], r3[12];
+    auto cell = [&](int o) -> uint32_t { return lat[ai + o]; };
+    r2[0] = cell(s2off(0));
+    r3[0] = cell(s3off(0));
+    r3[1] = cell(s3off(1));
+    r3[4] = cell(s3off(4));
+    r3[5] = cell(s3off(5));
+    r3[9] = cell(s3off(9));
+    r3[10] = cell(s3off(10));
+    if constexpr (SUB == 0) {
+        r3[11] = cell(s3off(11));
+        r2[1] = w.c[0]; r2[2] = w.c[3]; r2[3] = w.xc[1]; r2[4] = w.c[5]; r2[5] = w.xc[3];
+        r3[2] = w.c[2]; r3[3] = w.xc[0]; r3[6] = w.c[4]; r3[7] = w.xc[2]; r3[8] = w.c[7];
+    } else {
+        r3[8] = cell(s3off(8));
+        r2[1] = w.a[6]; r2[2] = w.xb[1]; r2[3] = w.a[5]; r2[4] = w.xb[3]; r2[5] = w.a[3];
+        r3[2] = w.xb[0]; r3[3] = w.a[4]; r3[6] = w.xb[2]; r3[7] = w.a[2]; r3[11] = w.a[1];
+    }
+    const uint32_t fresh = cell(SUB == 0 ? 1 + kP + kPP : 1 - kP - kPP);
+    // the partner's cells beyond the site's: the far one, 3 second and 9 third neighbours
+    uint32_t q0, q2[3], q3[9];
+    if constexpr (E == (SUB == 0 ? 7 : 1)) q0 = fresh;
+    else q0 = cell(dx + dy * kP + dz * kPP);
+    constexpr int jx = SUB == 0 ? ex - 1 : ex, jy = SUB == 0 ? ey - 1 : ey, jz = SUB == 0 ? ez - 1 : ez;
+    q2[0] = other_cell<SUB, jx + dx, jy, jz>(lat, ai, w);
+    q2[1] = other_cell<SUB, jx, jy + dy, jz>(lat, ai, w);
+    q2[2] = other_cell<SUB, jx, jy, jz + dz>(lat, ai, w);
+    q3[0] = other_cell<SUB, jx + dx, jy + dy, jz>(lat, ai, w);
+    q3[1] = other_cell<SUB, jx + dx, jy - dy, jz>(lat, ai, w);
+    q3[2] = other_cell<SUB, jx - dx, jy + dy, jz>(lat, ai, w);
+    q3[3] = other_cell<SUB, jx + dx, jy, jz + dz>(lat, ai, w);
+    q3[4] = other_cell<SUB, jx + dx, jy, jz - dz>(lat, ai, w);
+    q3[5] = other_cell<SUB, jx - dx, jy, jz + dz>(lat, ai, w);
+    q3[6] = other_cell<SUB, jx, jy + dy, jz + dz>(lat, ai, w);
+    q3[7] = other_cell<SUB, jx, jy + dy, jz - dz>(lat, ai, w);
+    q3[8] = other_cell<SUB, jx, jy - dy, jz + dz>(lat, ai, w);
+    const int32_t* wp = weight_row<KMAX>(wtab, ci, cj);
+    int32_t row[3 * kMaxS + 1];
+    if constexpr (DOT) {
+#pragma unroll
+        for (int k = 0; k < 3 * kMaxS + 1; ++k) row[k] = wp[k * kPlane];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- counts ----
+    // Species histograms of both neighbourhoods (the partner is counted in
+    // the first shell of i and i in that of j; the constant term undoes it).
+    const Edges edges = edges_of(u, ln2kT);   // depends on the draw only
+    uint32_t hi[kMaxS], hj[kMaxS];
+#pragma unroll
+    for (int s = 0; s < kMaxS; ++s) { hi[s] = kFieldBias<KMAX, DOT>; hj[s] = 0u; }
+    uint32_t T0 = 0u, T1 = 0u;   // the site's first shell, indices of even / odd popcount
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (__builtin_popcount(k) & 1) count1<false>(T1, s1[k]);
+        else count1<false>(T0, s1[k]);
+    }
+    hi[0] += T0 + T1;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) count1<false>(hi[1], r2[k]);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) count1<false>(hi[2], r3[k]);
+    uint32_t (&h)[kMaxS] = DIFF ? hi : hj;   // j's counts: subtracted from i's in the difference form
+    uint32_t t_same = odd ? T1 : T0, t_other = odd ? T0 : T1;
+    count1<true>(t_same, cj);         // j's third-shell cells among the site's first shell
+    count1<true>(t_other, s1[E ^ 7]); // j's second-shell cells among them
+    count1<DIFF>(h[0], ci);
+    count1<DIFF>(h[0], r2[ex ? 0 : 1]);
+    count1<DIFF>(h[0], r2[ey ? 2 : 3]);
+    count1<DIFF>(h[0], r2[ez ? 4 : 5]);
+    count1<DIFF>(h[0], r3[(ex ? 0 : 2) + (ey ? 0 : 1)]);
+    count1<DIFF>(h[0], r3[4 + (ex ? 0 : 2) + (ez ? 0 : 1)]);
+    count1<DIFF>(h[0], r3[8 + (ey ? 0 : 2) + (ez ? 0 : 1)]);
+    count1<DIFF>(h[0], q0);
+    h[1] = DIFF ? h[1] - t_other : h[1] + t_other;
+    h[2] = DIFF ? h[2] - t_same : h[2] + t_same;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) count1<DIFF>(h[1], q2[k]);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) count1<DIFF>(h[2], q3[k]);
+
+    const int32_t dE = energy_change<KMAX, 3, MODE>(hi, hj, row, wp);
+    const uint64_t acc = accepted_lanes(dE, u, edges, valid, tab);
+    // Both bytes are stored by every lane (unchanged unless accepted): no two
+    // lanes of a round touch the same byte.
+    const bool accept = __builtin_amdgcn_inverse_ballot_w64(acc);
+    const uint32_t ci_new = accept ? cj : ci, cj_new = accept ? ci : cj;
+    lat[ai] = (uint8_t)ci_new;
+    lat[ai + s1off<SUB>(E)] = (uint8_t)cj_new;
+    sums.dE += accept ? dE : 0;   // (0 for equal species: their row is zero)
+    sums.nacc += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ci != cj) & acc);
+
+    // ---- the window of the next trial ----
+    s1[E] = cj_new;
+    if constexpr (SUB == 0) {
+        w.c[0] = ci_new;
+        w.c[1] = r2[0];
+        w.c[2] = r2[2];
+        w.c[3] = r3[0];
+        w.c[4] = r2[4];
+        w.c[5] = r3[4];
+        w.c[6] = r3[8];
+        w.c[7] = fresh;
+        w.xc[0] = r2[3];
+        w.xc[1] = r3[1];
+        w.xc[2] = r2[5];
+        w.xc[3] = r3[5];
+    } else {
+        w.a[0] = r3[11];
+        w.a[1] = fresh;
+        w.a[2] = r2[5];
+        w.a[3] = r3[5];
+        w.a[4] = r2[3];
+        w.a[5] = r3[1];
+        w.a[6] = ci_new;
+        w.a[7] = r2[0];
+        w.xb[0] = r2[2];
+        w.xb[1] = r3[0];
+        w.xb[2] = r2[4];
+        w.xb[3] = r3[4];
+    }
+}
+
+// One trial with one or two shells, direction e (wave-uniform): the partner
+// and both neighbourhoods are loaded.
+template <int KMAX, int SMAX, int SUB, int MODE>
+__device__ __forceinline__ void trial12(uint8_t* lat, int ai, uint32_t u, int e, uint64_t valid, const int32_t* wtab,
+                                        const double* tab, float ln2kT, Sums& sums)
+{
+    constexpr bool DOT = MODE == kWtabDot;
+    constexpr bool DIFF = DOT || Field<KMAX>::F == 5;
+    const int aj = ai + s1base<SUB>() + (e & 1) + ((e >> 1) & 1) * kP + ((e >> 2) & 1) * kPP;
+    const uint32_t ci = lat[ai], cj = lat[aj];
+    uint32_t n1[8], n2[6], p1[8], p2[6];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        n1[k] = lat[ai + s1off<SUB>(k)];
+        p1[k] = lat[aj + s1off<1 - SUB>(k)];
+    }
+    if constexpr (SMAX == 2) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            n2[k] = lat[ai + s2off(k)];
+            p2[k] = lat[aj + s2off(k)];
+        }
+    }
+    const int32_t* wp = weight_row<KMAX>(wtab, ci, cj);
+    int32_t row[3 * kMaxS + 1];
+    if constexpr (DOT) {
+#pragma unroll
+        for (int k = 0; k < 3 * SMAX + 1; ++k) row[k] = wp[k * kPlane];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const Edges edges = edges_of(u, ln2kT);
+    uint32_t hi[kMaxS], hj[kMaxS];
+#pragma unroll
+    for (int s = 0; s < kMaxS; ++s) { hi[s] = kFieldBias<KMAX, DOT>; hj[s] = 0u; }
+    uint32_t (&h)[kMaxS] = DIFF ? hi : hj;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        count1<false>(hi[0], n1[k]);
+        count1<DIFF>(h[0], p1[k]);
+    }
+    if constexpr (SMAX == 2) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            count1<false>(hi[1], n2[k]);
+            count1<DIFF>(h[1], p2[k]);
+        }
+    }
+    const int32_t dE = energy_change<KMAX, SMAX, MODE>(hi, hj, row, wp);
+    const uint64_t acc = accepted_lanes(dE, u, edges, valid, tab);
+    const bool accept = __builtin_amdgcn_inverse_ballot_w64(acc);
+    lat[ai] = (uint8_t)(accept ? cj : ci);
+    lat[aj] = (uint8_t)(accept ? ci : cj);
+    sums.dE += accept ? dE : 0;
+    sums.nacc += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ci != cj) & acc);
+}
+
+// One trial with the round's direction e.
+template <int KMAX, int SMAX, int SUB, int MODE>
+__device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, uint64_t valid, const int32_t* wtab,
+                                      const double* tab, float ln2kT, Sums& sums, Window& w)
 {
     if constexpr (SMAX == 3) {
         switch (e) {
-        case 0: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 0>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        case 1: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 1>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        case 2: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 2>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        case 3: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 3>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        case 4: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 4>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        case 5: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 5>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        case 6: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 6>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
-        default: trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, 7>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy); break;
+        case 0: trial3<KMAX, SUB, MODE, 0>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 1: trial3<KMAX, SUB, MODE, 1>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 2: trial3<KMAX, SUB, MODE, 2>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 3: trial3<KMAX, SUB, MODE, 3>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 4: trial3<KMAX, SUB, MODE, 4>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 5: trial3<KMAX, SUB, MODE, 5>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 6: trial3<KMAX, SUB, MODE, 6>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        default: trial3<KMAX, SUB, MODE, 7>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
         }
     } else {
-        trial_dir<KMAX, SMAX, SUB, MODE, CIN, COUT, -1>(lat, ai, u, e, valid, wtab, tab, ln2kT, dEsum, nacc, cy);
+        trial12<KMAX, SMAX, SUB, MODE>(lat, ai, u, e, valid, wtab, tab, ln2kT, sums);
     }
 }
 
@@ -440,60 +498,75 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     uint32_t base_lo, base_hi;
     bcc_base_cell<SLAB>(B, D.z_off, ix, iy, iz, base_lo, base_hi);
     int64_t dEsum = 0;
-    uint32_t nacc = 0;
+    Sums sums = {0, 0u};
     const float ln2kT = (float)g_tab[kTabLn2kT];
     // The rounds, instantiated for each form of the weight rows (byte-dot or
     // full for KMAX <= 5, folded or full above): the form is per lattice, so
     // each instance stays branch-free.
     auto all_rounds = [&](auto mode_tag) {
         constexpr int MODE = decltype(mode_tag)::value;
-        // rounds of residue class m (corner then body) with draws uc, ub, the
-        // y/z steps of sub-colours 2m, 2m+1 in b4 (bits 0-1, 2-3) and their x
-        // steps in bits 2m, 2m+1 of pb.x
-        // Carries (three shells only: they hand on second and third
-        // neighbours): corner -> body of every class, and body -> corner of
-        // the next class when that is one cell on in x (rx = 1, 2).
-        constexpr bool CARRY = SMAX == 3;
-        Carry cy;
-        auto rounds = [&](int m, uint32_t uc, uint32_t ub, uint32_t b4) {
-            const int rx = m % 3, ry = (m / 3) % 3, rz = m / 9;
-            const bool valid = (3 * ix < B.wx - rx) & (3 * iy < B.wy - ry) & (3 * iz < B.wz - rz);
-            const int ac = lane_c + (rz * kPP + ry * kP + rx);
-            const uint32_t xb = (uint32_t)(pb.x >> (2 * m));
-            const int e0 = (int)(xb & 1u) | (int)(b4 & 3u) << 1;
-            const int e1 = (int)((xb >> 1) & 1u) | (int)((b4 >> 2) & 3u) << 1;
-            if (CARRY && rx == 0) {   // wave-uniform: no carry into the first class of an x row
-#pragma unroll
-                for (int e = 0; e < 8; ++e) cy.s1[e] = lat[ac + s1off<0>(e)];
-                cy.own = lat[ac];
-            }
-            trial<KMAX, SMAX, 0, MODE, CARRY, CARRY>(lat, ac, uc, e0, valid, s_w, g_tab, ln2kT, dEsum, nacc, cy);
-            __builtin_amdgcn_wave_barrier();
-            trial<KMAX, SMAX, 1, MODE, CARRY, CARRY>(lat, ac + kBodyFromCorner, ub, e1, valid, s_w, g_tab, ln2kT,
-                                                     dEsum, nacc, cy);
-            __builtin_amdgcn_wave_barrier();
-        };
-        // One copy of the round code serves all 27 classes (loops that are
+        Window win;
+        // One copy of the round code serves all 27 classes (a loop that is
         // not unrolled): the code a wave runs per round then stays small
-        // enough for the instruction cache, which the CU's waves, each at
-        // its own round, share.  The call for the next pair is made ahead
-        // of the pair's rounds (for class 26 it is made and not used).
+        // enough for the instruction cache, which the CU's waves, each at its
+        // own round, share.  The Philox call of the next pair of classes is
+        // made ahead of the pair's rounds (for class 26 it is made and not
+        // used).
         uint32_t w[4] = {base_lo, base_hi, s, (uint32_t)colour};
         philox4x32_10(w, k0, k1);
+        uint32_t u0 = 0u, u1 = 0u, u2 = 0u, u3 = 0u;
+        int rx = 0, ry = 0, rz = 0, ac = lane_c;
+        uint64_t valid_yz = 0;
 #pragma nounroll
-        for (int k = 0; k < 14; ++k) {
-            uint32_t u0 = w[0], u1 = w[1], u2 = w[2], u3 = w[3];
-            w[0] = base_lo; w[1] = base_hi; w[2] = s; w[3] = (uint32_t)colour + 256u * (uint32_t)(k + 1);
-            philox4x32_10(w, k0, k1);
-            // partner bits of sub-colours 4k .. 4k+3: bits 8k .. 8k+7
-            uint32_t bits = (uint32_t)(8 * k < 64 ? pb.yz_lo >> (8 * k) : pb.yz_hi >> (8 * k - 64));
-            const int nj = k < 13 ? 2 : 1;
-#pragma nounroll
-            for (int j = 0; j < nj; ++j) {
-                rounds(2 * k + j, u0, u1, bits);
+        for (int m = 0; m < 27; ++m) {
+            if (m & 1) {
                 u0 = u2;
                 u1 = u3;
-                bits >>= 4;
+            } else {
+                u0 = w[0]; u1 = w[1]; u2 = w[2]; u3 = w[3];
+                w[0] = base_lo; w[1] = base_hi; w[2] = s; w[3] = (uint32_t)colour + 256u * (uint32_t)(m / 2 + 1);
+                philox4x32_10(w, k0, k1);
+            }
+            // partner directions of sub-colours 2m, 2m + 1
+            const uint32_t xb = (uint32_t)(pb.x >> (2 * m));
+            const uint32_t b4 = (uint32_t)(m < 16 ? pb.yz_lo >> (4 * m) : pb.yz_hi >> (4 * m - 64));
+            const int e0 = (int)(xb & 1u) | (int)(b4 & 3u) << 1;
+            const int e1 = (int)((xb >> 1) & 1u) | (int)((b4 >> 2) & 3u) << 1;
+            if (rx == 0) {   // a new x row of classes
+                valid_yz = __builtin_amdgcn_ballot_w64((3 * iy < B.wy - ry) & (3 * iz < B.wz - rz));
+                if constexpr (SMAX == 3) {
+                    const uint8_t* p = lat + ac;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        win.a[e] = p[s1off<0>(e)];
+                        if (e != 6) win.c[e] = p[(e & 1) - 1 + (e >> 1 & 1) * kP + (e >> 2) * kPP];
+                    }
+                    win.c[6] = 0u;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        win.xc[k] = p[k - 1 - kP];
+                        win.xc[k + 2] = p[k - 1 - kPP];
+                        win.xb[k] = p[WavePitch::kBodyFromCorner + k - 1 + kP];
+                        win.xb[k + 2] = p[WavePitch::kBodyFromCorner + k - 1 + kPP];
+                    }
+                }
+            }
+            const uint64_t valid = valid_yz & __builtin_amdgcn_ballot_w64(3 * ix < B.wx - rx);
+            trial<KMAX, SMAX, 0, MODE>(lat, ac, u0, e0, valid, s_w, g_tab, ln2kT, sums, win);
+            __builtin_amdgcn_wave_barrier();
+            trial<KMAX, SMAX, 1, MODE>(lat, ac + kBodyFromCorner, u1, e1, valid, s_w, g_tab, ln2kT, sums, win);
+            __builtin_amdgcn_wave_barrier();
+            dEsum += (int64_t)sums.dE;
+            sums.dE = 0;
+            ++ac;
+            if (++rx == 3) {
+                rx = 0;
+                ac += kP - 3;
+                if (++ry == 3) {
+                    ry = 0;
+                    ++rz;
+                    ac += kPP - 3 * kP;
+                }
             }
         }
     };
@@ -513,7 +586,7 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
 
     // ---- wavefront reduction of the energy change and accepted count ----
     uint64_t sum = (uint64_t)dEsum;
-    const uint32_t cnt = nacc;   // already the wave's total
+    const uint32_t cnt = sums.nacc;   // already the wave's total
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         const uint32_t lo = __shfl_xor((uint32_t)sum, o, kWave);
