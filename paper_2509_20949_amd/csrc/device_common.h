@@ -44,6 +44,48 @@ template <bool NEG> __device__ __forceinline__ void count1(uint32_t& h, uint32_t
     else asm("v_lshl_add_u32 %0, 1, %1, %0" : "+v"(h) : "v"(c));
 }
 
+// Two to four counts of one chain in one asm block: between asm blocks that
+// write and read one register the compiler puts a wait state (it cannot see
+// that the shift-add writes the whole register), an issue slot each.
+#define SMCX_COUNT(S, N) "v_lshl_add_u32 %0, " S ", %" N ", %0\n\t"
+template <bool NEG> __device__ __forceinline__ void count2(uint32_t& h, uint32_t a, uint32_t b)
+{
+    if constexpr (NEG) asm(SMCX_COUNT("-1", "1") SMCX_COUNT("-1", "2") : "+&v"(h) : "v"(a), "v"(b));
+    else asm(SMCX_COUNT("1", "1") SMCX_COUNT("1", "2") : "+&v"(h) : "v"(a), "v"(b));
+}
+template <bool NEG> __device__ __forceinline__ void count3(uint32_t& h, uint32_t a, uint32_t b, uint32_t c)
+{
+    if constexpr (NEG)
+        asm(SMCX_COUNT("-1", "1") SMCX_COUNT("-1", "2") SMCX_COUNT("-1", "3") : "+&v"(h) : "v"(a), "v"(b), "v"(c));
+    else
+        asm(SMCX_COUNT("1", "1") SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") : "+&v"(h) : "v"(a), "v"(b), "v"(c));
+}
+template <bool NEG> __device__ __forceinline__ void count4(uint32_t& h, uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    if constexpr (NEG)
+        asm(SMCX_COUNT("-1", "1") SMCX_COUNT("-1", "2") SMCX_COUNT("-1", "3") SMCX_COUNT("-1", "4")
+            : "+&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d));
+    else
+        asm(SMCX_COUNT("1", "1") SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") SMCX_COUNT("1", "4")
+            : "+&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d));
+}
+// A chain's first four counts, from 0 or from a wave-uniform start.
+__device__ __forceinline__ uint32_t count4_from0(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    uint32_t h;
+    asm("v_lshl_add_u32 %0, 1, %1, 0\n\t" SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") SMCX_COUNT("1", "4")
+        : "=&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d));
+    return h;
+}
+__device__ __forceinline__ uint32_t count4_from(uint32_t start, uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    uint32_t h;
+    asm("v_lshl_add_u32 %0, 1, %1, %5\n\t" SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") SMCX_COUNT("1", "4")
+        : "=&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d), "s"(start));
+    return h;
+}
+#undef SMCX_COUNT
+
 // LDS form of the pair-weight table: entry f of row (a, b) (f = s*KMAX + p
 // for a weight, SMAX*KMAX for the constant) sits in plane f at position
 // a*KMAX + b, planes wplane(KMAX) dwords apart.  The lanes of a wave read one

@@ -89,8 +89,40 @@ __device__ __forceinline__ uint32_t weigh(const uint32_t (&hi)[kMaxS], const uin
 // cell of it within the x row: in units of a/2, trials of one round are 6
 // apart and change cells within 1, the window reaches 4 ahead of the row's
 // first site and 3 behind, on the axes and sides where it holds cells.
+//   pc, pb the packed counts (with the fields' bias) of the four cells of a
+//          plane around the row's axis -- (x, y +- 1, z), (x, y, z +- 1) --
+//          for the planes x - 1 and x of the corner (body) sublattice: four
+//          third neighbours of the site one plane on, four second neighbours
+//          of the plane's own site and four third neighbours of the next.
 struct Window {
-    uint32_t a[8], c[8], xb[4], xc[4];
+    uint32_t a[8], c[8], xb[4], xc[4], pc[2], pb[2];
+    // The window before the corner trial at p = corner(x, y, z).
+    __device__ __forceinline__ void load(const uint8_t* p, uint32_t bias)
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            a[e] = p[kS1Corner + (e & 1) + (e >> 1 & 1) * kP + (e >> 2) * kPP];
+            c[e] = e == 6 ? 0u : p[(e & 1) - 1 + (e >> 1 & 1) * kP + (e >> 2) * kPP];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            xc[k] = p[k - 1 - kP];
+            xc[k + 2] = p[k - 1 - kPP];
+            xb[k] = p[WavePitch::kBodyFromCorner + k - 1 + kP];
+            xb[k + 2] = p[WavePitch::kBodyFromCorner + k - 1 + kPP];
+        }
+        // (hides from the compiler that the entries come from byte loads: it
+        // would carry bytes and extend each again in every trial)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) asm("" : "+v"(a[k]), "+v"(c[k]));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) asm("" : "+v"(xb[k]), "+v"(xc[k]));
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            pc[k] = count4_from(bias, c[2 + k], xc[k], c[4 + k], xc[2 + k]);
+            pb[k] = count4_from(bias, xb[k], a[4 + k], xb[2 + k], a[2 + k]);
+        }
+    }
 };
 
 // The code of the cell (I, J, K) from the site's cell in the other
@@ -104,6 +136,27 @@ __device__ __forceinline__ uint32_t other_cell(const uint8_t* lat, int ai, const
     else if constexpr (SUB == 1 && (I == 0 || I == 1) && J == -1 && K == 0) return w.xc[I];
     else if constexpr (SUB == 1 && (I == 0 || I == 1) && J == 0 && K == -1) return w.xc[I + 2];
     else return lat[ai + kCell];
+}
+
+// The cells of the site's own sublattice that a three-shell trial loads,
+// whatever its direction: second and third neighbours (indices as s2off,
+// s3off) and the cell that completes the next trial's first shell.
+struct OwnCells {
+    uint32_t r2_0, r3_0, r3_1, r3_4, r3_5, r3_8or11, r3_9, r3_10, fresh;
+};
+template <int SUB> __device__ __forceinline__ OwnCells load_own(const uint8_t* p)
+{
+    OwnCells o;
+    o.r2_0 = p[s2off(0)];
+    o.r3_0 = p[s3off(0)];
+    o.r3_1 = p[s3off(1)];
+    o.r3_4 = p[s3off(4)];
+    o.r3_5 = p[s3off(5)];
+    o.r3_9 = p[s3off(9)];
+    o.r3_10 = p[s3off(10)];
+    o.r3_8or11 = p[s3off(SUB == 0 ? 11 : 8)];
+    o.fresh = p[SUB == 0 ? 1 + kP + kPP : 1 - kP - kPP];
+    return o;
 }
 
 // The Metropolis test of Eq. (3) for the draw u as two edges on float(dE):
@@ -161,7 +214,7 @@ __device__ __forceinline__ int32_t energy_change(const uint32_t (&hi)[kMaxS], co
         // chain: ((A2 * 256 + A1) * 256 + constant) + A0
         int32_t d[kMaxS];
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) d[s] = (int32_t)(hi[s] & 0x7fffffffu);
+        for (int s = 0; s < SMAX; ++s) d[s] = (int32_t)(KMAX == 5 ? hi[s] & 0x7fffffffu : hi[s]);   // (K <= 4: byte 3 weighs nothing)
         int32_t X = 0;
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(d[s], row[3 * s + 2], X, false);
@@ -211,8 +264,8 @@ constexpr uint32_t kFieldBias = DOT ? 0x20202020u
 // first-shell counts over indices of even and odd popcount, those two sets are
 // T[par E ^ 1] less cell E ^ 7 and T[par E] less cell E (the partner).
 template <int KMAX, int SUB, int MODE, int E>
-__device__ __forceinline__ void trial3(uint8_t* lat, int ai, uint32_t u, uint64_t valid, const int32_t* wtab,
-                                       const double* tab, float ln2kT, Sums& sums, Window& w)
+__device__ __forceinline__ void trial3(uint8_t* lat, int ai, const OwnCells& o, uint32_t u, uint64_t valid,
+                                       const int32_t* wtab, const double* tab, float ln2kT, Sums& sums, Window& w)
 {
     constexpr bool DOT = MODE == kWtabDot;
     // 5-bit fields (and the byte-dot form) hold bias + n_i - n_j without
@@ -225,32 +278,29 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, uint32_t u, uint64_
     uint32_t (&s1)[8] = SUB == 0 ? w.a : w.c;
     const uint32_t ci = SUB == 0 ? w.c[1] : w.a[7], cj = s1[E];
 
-    // ---- every load of the trial, then every count ----
-    // the site's second and third neighbours (indices as s2off, s3off) and
-    // the cell that completes the next trial's first shell
+    // ---- the rest of the trial's loads (o: those of every direction), then
+    // every count ----
     uint32_t r2[6], r3[12];
-    auto cell = [&](int o) -> uint32_t { return lat[ai + o]; };
-    r2[0] = cell(s2off(0));
-    r3[0] = cell(s3off(0));
-    r3[1] = cell(s3off(1));
-    r3[4] = cell(s3off(4));
-    r3[5] = cell(s3off(5));
-    r3[9] = cell(s3off(9));
-    r3[10] = cell(s3off(10));
+    r2[0] = o.r2_0;
+    r3[0] = o.r3_0;
+    r3[1] = o.r3_1;
+    r3[4] = o.r3_4;
+    r3[5] = o.r3_5;
+    r3[9] = o.r3_9;
+    r3[10] = o.r3_10;
     if constexpr (SUB == 0) {
-        r3[11] = cell(s3off(11));
+        r3[11] = o.r3_8or11;
         r2[1] = w.c[0]; r2[2] = w.c[3]; r2[3] = w.xc[1]; r2[4] = w.c[5]; r2[5] = w.xc[3];
         r3[2] = w.c[2]; r3[3] = w.xc[0]; r3[6] = w.c[4]; r3[7] = w.xc[2]; r3[8] = w.c[7];
     } else {
-        r3[8] = cell(s3off(8));
+        r3[8] = o.r3_8or11;
         r2[1] = w.a[6]; r2[2] = w.xb[1]; r2[3] = w.a[5]; r2[4] = w.xb[3]; r2[5] = w.a[3];
         r3[2] = w.xb[0]; r3[3] = w.a[4]; r3[6] = w.xb[2]; r3[7] = w.a[2]; r3[11] = w.a[1];
     }
-    const uint32_t fresh = cell(SUB == 0 ? 1 + kP + kPP : 1 - kP - kPP);
     // the partner's cells beyond the site's: the far one, 3 second and 9 third neighbours
     uint32_t q0, q2[3], q3[9];
-    if constexpr (E == (SUB == 0 ? 7 : 1)) q0 = fresh;
-    else q0 = cell(dx + dy * kP + dz * kPP);
+    if constexpr (E == (SUB == 0 ? 7 : 1)) q0 = o.fresh;
+    else q0 = lat[ai + dx + dy * kP + dz * kPP];
     constexpr int jx = SUB == 0 ? ex - 1 : ex, jy = SUB == 0 ? ey - 1 : ey, jz = SUB == 0 ? ez - 1 : ez;
     q2[0] = other_cell<SUB, jx + dx, jy, jz>(lat, ai, w);
     q2[1] = other_cell<SUB, jx, jy + dy, jz>(lat, ai, w);
@@ -276,38 +326,34 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, uint32_t u, uint64_
     // Species histograms of both neighbourhoods (the partner is counted in
     // the first shell of i and i in that of j; the constant term undoes it).
     const Edges edges = edges_of(u, ln2kT);   // depends on the draw only
-    uint32_t hi[kMaxS], hj[kMaxS];
-#pragma unroll
-    for (int s = 0; s < kMaxS; ++s) { hi[s] = kFieldBias<KMAX, DOT>; hj[s] = 0u; }
-    uint32_t T0 = 0u, T1 = 0u;   // the site's first shell, indices of even / odd popcount
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        if (__builtin_popcount(k) & 1) count1<false>(T1, s1[k]);
-        else count1<false>(T0, s1[k]);
-    }
-    hi[0] += T0 + T1;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) count1<false>(hi[1], r2[k]);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) count1<false>(hi[2], r3[k]);
+    // Cells of the window first, then the loaded ones in load order.
+    constexpr uint32_t bias = kFieldBias<KMAX, DOT>;
+    uint32_t hi[kMaxS], hj[kMaxS] = {0u, 0u, 0u};
+    // the site's first shell, indices of even / odd popcount
+    const uint32_t T0 = count4_from0(s1[0], s1[3], s1[5], s1[6]), T1 = count4_from0(s1[1], s1[2], s1[4], s1[7]);
+    hi[0] = T0 + T1 + bias;
+    // second and third shell: the plane sums of the window, the next plane's,
+    // and the cells at dx = 0 of the third shell
+    uint32_t (&mine)[2] = SUB == 0 ? w.pc : w.pb;
+    uint32_t (&others)[2] = SUB == 0 ? w.pb : w.pc;
+    const uint32_t next_plane = count4_from(bias, r3[0], r3[1], r3[4], r3[5]);
+    hi[2] = count4_from(0u - bias, r3[8], r3[9], r3[10], r3[11]);
+    hi[2] += mine[0] + next_plane;
+    hi[1] = mine[1];
+    count2<false>(hi[1], r2[1], r2[0]);
     uint32_t (&h)[kMaxS] = DIFF ? hi : hj;   // j's counts: subtracted from i's in the difference form
     uint32_t t_same = odd ? T1 : T0, t_other = odd ? T0 : T1;
     count1<true>(t_same, cj);         // j's third-shell cells among the site's first shell
     count1<true>(t_other, s1[E ^ 7]); // j's second-shell cells among them
-    count1<DIFF>(h[0], ci);
-    count1<DIFF>(h[0], r2[ex ? 0 : 1]);
-    count1<DIFF>(h[0], r2[ey ? 2 : 3]);
-    count1<DIFF>(h[0], r2[ez ? 4 : 5]);
-    count1<DIFF>(h[0], r3[(ex ? 0 : 2) + (ey ? 0 : 1)]);
-    count1<DIFF>(h[0], r3[4 + (ex ? 0 : 2) + (ez ? 0 : 1)]);
-    count1<DIFF>(h[0], r3[8 + (ey ? 0 : 2) + (ez ? 0 : 1)]);
-    count1<DIFF>(h[0], q0);
+    count4<DIFF>(h[0], ci, r2[ex ? 0 : 1], r2[ey ? 2 : 3], r2[ez ? 4 : 5]);
+    count4<DIFF>(h[0], r3[(ex ? 0 : 2) + (ey ? 0 : 1)], r3[4 + (ex ? 0 : 2) + (ez ? 0 : 1)],
+                 r3[8 + (ey ? 0 : 2) + (ez ? 0 : 1)], q0);
     h[1] = DIFF ? h[1] - t_other : h[1] + t_other;
     h[2] = DIFF ? h[2] - t_same : h[2] + t_same;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) count1<DIFF>(h[1], q2[k]);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) count1<DIFF>(h[2], q3[k]);
+    count3<DIFF>(h[1], q2[0], q2[1], q2[2]);
+    count3<DIFF>(h[2], q3[0], q3[1], q3[2]);
+    count3<DIFF>(h[2], q3[3], q3[4], q3[5]);
+    count3<DIFF>(h[2], q3[6], q3[7], q3[8]);
 
     const int32_t dE = energy_change<KMAX, 3, MODE>(hi, hj, row, wp);
     const uint64_t acc = accepted_lanes(dE, u, edges, valid, tab);
@@ -322,6 +368,12 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, uint32_t u, uint64_
 
     // ---- the window of the next trial ----
     s1[E] = cj_new;
+    if constexpr (E == 2 || E == 3 || E == 4 || E == 5) {   // the partner is a cell of a plane sum
+        count1<false>(others[E & 1], cj_new);
+        count1<true>(others[E & 1], cj);
+    }
+    mine[0] = mine[1];
+    mine[1] = next_plane;
     if constexpr (SUB == 0) {
         w.c[0] = ci_new;
         w.c[1] = r2[0];
@@ -330,14 +382,14 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, uint32_t u, uint64_
         w.c[4] = r2[4];
         w.c[5] = r3[4];
         w.c[6] = r3[8];
-        w.c[7] = fresh;
+        w.c[7] = o.fresh;
         w.xc[0] = r2[3];
         w.xc[1] = r3[1];
         w.xc[2] = r2[5];
         w.xc[3] = r3[5];
     } else {
         w.a[0] = r3[11];
-        w.a[1] = fresh;
+        w.a[1] = o.fresh;
         w.a[2] = r2[5];
         w.a[3] = r3[5];
         w.a[4] = r2[3];
@@ -382,21 +434,18 @@ __device__ __forceinline__ void trial12(uint8_t* lat, int ai, uint32_t u, int e,
     }
     __builtin_amdgcn_sched_barrier(0);
     const Edges edges = edges_of(u, ln2kT);
-    uint32_t hi[kMaxS], hj[kMaxS];
-#pragma unroll
-    for (int s = 0; s < kMaxS; ++s) { hi[s] = kFieldBias<KMAX, DOT>; hj[s] = 0u; }
+    constexpr uint32_t bias = kFieldBias<KMAX, DOT>;
+    uint32_t hi[kMaxS], hj[kMaxS] = {0u, 0u, 0u};
     uint32_t (&h)[kMaxS] = DIFF ? hi : hj;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        count1<false>(hi[0], n1[k]);
-        count1<DIFF>(h[0], p1[k]);
-    }
+    hi[0] = count4_from(bias, n1[0], n1[1], n1[2], n1[3]);
+    count4<false>(hi[0], n1[4], n1[5], n1[6], n1[7]);
+    count4<DIFF>(h[0], p1[0], p1[1], p1[2], p1[3]);
+    count4<DIFF>(h[0], p1[4], p1[5], p1[6], p1[7]);
     if constexpr (SMAX == 2) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            count1<false>(hi[1], n2[k]);
-            count1<DIFF>(h[1], p2[k]);
-        }
+        hi[1] = count4_from(bias, n2[0], n2[1], n2[2], n2[3]);
+        count2<false>(hi[1], n2[4], n2[5]);
+        count3<DIFF>(h[1], p2[0], p2[1], p2[2]);
+        count3<DIFF>(h[1], p2[3], p2[4], p2[5]);
     }
     const int32_t dE = energy_change<KMAX, SMAX, MODE>(hi, hj, row, wp);
     const uint64_t acc = accepted_lanes(dE, u, edges, valid, tab);
@@ -413,15 +462,16 @@ __device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, u
                                       const double* tab, float ln2kT, Sums& sums, Window& w)
 {
     if constexpr (SMAX == 3) {
+        const OwnCells o = load_own<SUB>(lat + ai);
         switch (e) {
-        case 0: trial3<KMAX, SUB, MODE, 0>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        case 1: trial3<KMAX, SUB, MODE, 1>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        case 2: trial3<KMAX, SUB, MODE, 2>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        case 3: trial3<KMAX, SUB, MODE, 3>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        case 4: trial3<KMAX, SUB, MODE, 4>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        case 5: trial3<KMAX, SUB, MODE, 5>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        case 6: trial3<KMAX, SUB, MODE, 6>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
-        default: trial3<KMAX, SUB, MODE, 7>(lat, ai, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 0: trial3<KMAX, SUB, MODE, 0>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 1: trial3<KMAX, SUB, MODE, 1>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 2: trial3<KMAX, SUB, MODE, 2>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 3: trial3<KMAX, SUB, MODE, 3>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 4: trial3<KMAX, SUB, MODE, 4>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 5: trial3<KMAX, SUB, MODE, 5>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        case 6: trial3<KMAX, SUB, MODE, 6>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
+        default: trial3<KMAX, SUB, MODE, 7>(lat, ai, o, u, valid, wtab, tab, ln2kT, sums, w); break;
         }
     } else {
         trial12<KMAX, SMAX, SUB, MODE>(lat, ai, u, e, valid, wtab, tab, ln2kT, sums);
@@ -506,67 +556,52 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     auto all_rounds = [&](auto mode_tag) {
         constexpr int MODE = decltype(mode_tag)::value;
         Window win;
-        // One copy of the round code serves all 27 classes (a loop that is
-        // not unrolled): the code a wave runs per round then stays small
-        // enough for the instruction cache, which the CU's waves, each at its
-        // own round, share.  The Philox call of the next pair of classes is
-        // made ahead of the pair's rounds (for class 26 it is made and not
-        // used).
-        uint32_t w[4] = {base_lo, base_hi, s, (uint32_t)colour};
-        philox4x32_10(w, k0, k1);
-        uint32_t u0 = 0u, u1 = 0u, u2 = 0u, u3 = 0u;
-        int rx = 0, ry = 0, rz = 0, ac = lane_c;
-        uint64_t valid_yz = 0;
+        // A loop over the nine x rows of classes, each row's three classes
+        // unrolled: the window's cells then change registers, not places (a
+        // loop over classes moved 14 of them per trial).  The row's code, 6 x
+        // 8 directions, is 36 KB of the 64 KB instruction cache that two CUs
+        // share; all waves of a launch run the same directions.
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        int ac = lane_c, ry = 0, rz = 0;
 #pragma nounroll
-        for (int m = 0; m < 27; ++m) {
-            if (m & 1) {
-                u0 = u2;
-                u1 = u3;
-            } else {
-                u0 = w[0]; u1 = w[1]; u2 = w[2]; u3 = w[3];
-                w[0] = base_lo; w[1] = base_hi; w[2] = s; w[3] = (uint32_t)colour + 256u * (uint32_t)(m / 2 + 1);
-                philox4x32_10(w, k0, k1);
-            }
-            // partner directions of sub-colours 2m, 2m + 1
-            const uint32_t xb = (uint32_t)(pb.x >> (2 * m));
-            const uint32_t b4 = (uint32_t)(m < 16 ? pb.yz_lo >> (4 * m) : pb.yz_hi >> (4 * m - 64));
-            const int e0 = (int)(xb & 1u) | (int)(b4 & 3u) << 1;
-            const int e1 = (int)((xb >> 1) & 1u) | (int)((b4 >> 2) & 3u) << 1;
-            if (rx == 0) {   // a new x row of classes
-                valid_yz = __builtin_amdgcn_ballot_w64((3 * iy < B.wy - ry) & (3 * iz < B.wz - rz));
-                if constexpr (SMAX == 3) {
-                    const uint8_t* p = lat + ac;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        win.a[e] = p[s1off<0>(e)];
-                        if (e != 6) win.c[e] = p[(e & 1) - 1 + (e >> 1 & 1) * kP + (e >> 2) * kPP];
-                    }
-                    win.c[6] = 0u;
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        win.xc[k] = p[k - 1 - kP];
-                        win.xc[k + 2] = p[k - 1 - kPP];
-                        win.xb[k] = p[WavePitch::kBodyFromCorner + k - 1 + kP];
-                        win.xb[k + 2] = p[WavePitch::kBodyFromCorner + k - 1 + kPP];
-                    }
+        for (int m0 = 0; m0 < 27; m0 += 3) {
+            const uint64_t valid_yz = __builtin_amdgcn_ballot_w64((3 * iy < B.wy - ry) & (3 * iz < B.wz - rz));
+            // partner directions: bits 2m, 2m + 1 of x, 4m .. 4m + 3 of yz
+            uint32_t xb = (uint32_t)(pb.x >> (2 * m0));
+            uint32_t b4 = (uint32_t)(m0 < 16 ? pb.yz_lo >> (4 * m0) : pb.yz_hi >> (4 * m0 - 64));
+            if (m0 == 15) b4 |= (uint32_t)pb.yz_hi << 4;   // (class 15 ends the low word)
+            if constexpr (SMAX == 3) win.load(lat + ac, kFieldBias<KMAX, MODE == kWtabDot>);
+            auto one_class = [&](auto rx_tag) {
+                constexpr int rx = decltype(rx_tag)::value;
+                // one Philox call per pair of classes
+                if (((m0 + rx) & 1) == 0) {
+                    w[0] = base_lo; w[1] = base_hi; w[2] = s;
+                    w[3] = (uint32_t)colour + 256u * (uint32_t)((m0 + rx) >> 1);
+                    philox4x32_10(w, k0, k1);
                 }
-            }
-            const uint64_t valid = valid_yz & __builtin_amdgcn_ballot_w64(3 * ix < B.wx - rx);
-            trial<KMAX, SMAX, 0, MODE>(lat, ac, u0, e0, valid, s_w, g_tab, ln2kT, sums, win);
-            __builtin_amdgcn_wave_barrier();
-            trial<KMAX, SMAX, 1, MODE>(lat, ac + kBodyFromCorner, u1, e1, valid, s_w, g_tab, ln2kT, sums, win);
-            __builtin_amdgcn_wave_barrier();
-            dEsum += (int64_t)sums.dE;
-            sums.dE = 0;
-            ++ac;
-            if (++rx == 3) {
-                rx = 0;
-                ac += kP - 3;
-                if (++ry == 3) {
-                    ry = 0;
-                    ++rz;
-                    ac += kPP - 3 * kP;
-                }
+                const uint32_t u0 = w[0], u1 = w[1];
+                w[0] = w[2];
+                w[1] = w[3];
+                const int e0 = (int)(xb & 1u) | (int)(b4 & 3u) << 1;
+                const int e1 = (int)((xb >> 1) & 1u) | (int)((b4 >> 2) & 3u) << 1;
+                xb >>= 2;
+                b4 >>= 4;
+                const uint64_t valid = valid_yz & __builtin_amdgcn_ballot_w64(3 * ix < B.wx - rx);
+                trial<KMAX, SMAX, 0, MODE>(lat, ac + rx, u0, e0, valid, s_w, g_tab, ln2kT, sums, win);
+                __builtin_amdgcn_wave_barrier();
+                trial<KMAX, SMAX, 1, MODE>(lat, ac + rx + kBodyFromCorner, u1, e1, valid, s_w, g_tab, ln2kT, sums, win);
+                __builtin_amdgcn_wave_barrier();
+                dEsum += (int64_t)sums.dE;
+                sums.dE = 0;
+            };
+            one_class(std::integral_constant<int, 0>{});
+            one_class(std::integral_constant<int, 1>{});
+            one_class(std::integral_constant<int, 2>{});
+            ac += kP;
+            if (++ry == 3) {
+                ry = 0;
+                ++rz;
+                ac += kPP - 3 * kP;
             }
         }
     };
