@@ -69,12 +69,12 @@ template <bool NEG> __device__ __forceinline__ void count4(uint32_t& h, uint32_t
         asm(SMCX_COUNT("1", "1") SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") SMCX_COUNT("1", "4")
             : "+&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d));
 }
-// A chain's first four counts, from 0 or from a wave-uniform start.
-__device__ __forceinline__ uint32_t count4_from0(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+// A chain's first counts, from 0 or from a wave-uniform start.
+__device__ __forceinline__ uint32_t count3_from0(uint32_t a, uint32_t b, uint32_t c)
 {
     uint32_t h;
-    asm("v_lshl_add_u32 %0, 1, %1, 0\n\t" SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") SMCX_COUNT("1", "4")
-        : "=&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d));
+    asm("v_lshl_add_u32 %0, 1, %1, 0\n\t" SMCX_COUNT("1", "2") SMCX_COUNT("1", "3")
+        : "=&v"(h) : "v"(a), "v"(b), "v"(c));
     return h;
 }
 __device__ __forceinline__ uint32_t count4_from(uint32_t start, uint32_t a, uint32_t b, uint32_t c, uint32_t d)
@@ -82,6 +82,19 @@ __device__ __forceinline__ uint32_t count4_from(uint32_t start, uint32_t a, uint
     uint32_t h;
     asm("v_lshl_add_u32 %0, 1, %1, %5\n\t" SMCX_COUNT("1", "2") SMCX_COUNT("1", "3") SMCX_COUNT("1", "4")
         : "=&v"(h) : "v"(a), "v"(b), "v"(c), "v"(d), "s"(start));
+    return h;
+}
+// start + (1 << a) + (1 << b), and start + (1 << a) - (1 << b).
+__device__ __forceinline__ uint32_t count2_onto(uint32_t start, uint32_t a, uint32_t b)
+{
+    uint32_t h;
+    asm("v_lshl_add_u32 %0, 1, %1, %3\n\t" SMCX_COUNT("1", "2") : "=&v"(h) : "v"(a), "v"(b), "v"(start));
+    return h;
+}
+__device__ __forceinline__ uint32_t count_swap(uint32_t start, uint32_t a, uint32_t b)
+{
+    uint32_t h;
+    asm("v_lshl_add_u32 %0, 1, %1, %3\n\t" SMCX_COUNT("-1", "2") : "=&v"(h) : "v"(a), "v"(b), "v"(start));
     return h;
 }
 #undef SMCX_COUNT
@@ -184,26 +197,26 @@ __device__ __forceinline__ void bstore16(__amdgpu_buffer_rsrc_t r, uint32_t off,
 // The exact test accepts an uphill change dE iff u < thr(dE), thr the FP64
 // table product, equal to 2^32 exp(-dE / k_B T) to a relative 1e-12.  Let x
 // be the energy with 2^32 exp(-x / k_B T) = u, x = (32 - log2 u) ln2 k_B T.
-// e below is x in FP32 from v_log_f32.  Over every u > 0 the device's
-// 32 - log2(float(u)) is within 2.0e-6 of 32 - log2(u) (checked for all
-// 2^32 draws by smcx_device_check_accept_bounds), so with c = ln2 k_B T
-// rounded to FP32 and x <= 32 c:  |e - x| <= 2.0e-6 c + 2^-23 x <= 1.8
-// micro-eV for T <= 5000 K.  e -+ M rounds to FP32 within 0.5 (e < 2^24)
-// and truncates to an integer, so with M = 8 the bound lo lies more than
-// 5.7 micro-eV below x and hi + 1 more than 4.7 above it: every dE <= lo
-// passes the exact test and every dE > hi fails it.  Only lo < dE <= hi
+// elo below is x - M in FP32 from v_log_f32, one fused multiply-add: over
+// every u > 0 the device's 32 - log2(float(u)) is within 2.0e-6 of
+// 32 - log2(u) (checked for all 2^32 draws by
+// smcx_device_check_accept_bounds), so with c = ln2 k_B T rounded to FP32 and
+// x <= 32 c the value before the two roundings is within 2.0e-6 c + 2^-24 x
+// <= 1.2 micro-eV of x - M for T <= 5000 K; 32 c - M and the result (below
+// 2^24) round by at most 0.5 each, and ehi = elo + 2 M by 0.5 more.  So with
+// M = 8 the bound lo = floor(elo) lies more than 5.8 micro-eV below x and
+// hi + 1, hi = floor(ehi), more than 4.3 above it: every dE <= lo passes the
+// exact test and every dE > hi fails it.  Only lo < dE <= hi
 // (and u = 0, where x is infinite but thr may underflow) need the table.
 // c = ln2 k_B T in micro-eV, as a float.
-// The sweep kernels compare float(dE) with the edges elo = e - M and
-// ehi = e + M: for an integer dE in (0, 2^24), float(dE) is exact, and
-// float(dE) <= elo iff dE <= lo = floor(elo), likewise for hi.  (u = 0:
-// e = +inf.)
+// The sweep kernels compare float(dE) with the edges elo and ehi: for an
+// integer dE in (0, 2^24), float(dE) is exact, and float(dE) <= elo iff
+// dE <= lo, likewise for hi.  (u = 0: both +inf.)
 constexpr float kAcceptMargin = 8.0f;
 __device__ __forceinline__ void accept_edges(uint32_t u, float c, float& elo, float& ehi)
 {
-    const float e = (32.0f - __builtin_amdgcn_logf((float)u)) * c;
-    elo = e - kAcceptMargin;
-    ehi = e + kAcceptMargin;
+    elo = __builtin_fmaf(-c, __builtin_amdgcn_logf((float)u), 32.0f * c - kAcceptMargin);
+    ehi = elo + 2.0f * kAcceptMargin;
 }
 // The same bounds as integers, lo = floor(elo) and hi = floor(ehi) (at most
 // 1e9; e >= 0, and the truncation is the floor wherever the bound is

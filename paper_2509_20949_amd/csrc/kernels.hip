@@ -260,9 +260,7 @@ constexpr uint32_t kFieldBias = DOT ? 0x20202020u
 // along the three axes, its third neighbours in the three planes with the same
 // signs, and the far cell i + 2 s.  j's second and third shells hold the
 // site's first-shell cells k with one or two direction bits flipped
-// (popcount(k ^ E) = 1 or 2) and 3 and 9 cells beyond.  With T0, T1 the site's
-// first-shell counts over indices of even and odd popcount, those two sets are
-// T[par E ^ 1] less cell E ^ 7 and T[par E] less cell E (the partner).
+// (popcount(k ^ E) = 1 or 2), counted once for both, and 3 and 9 cells beyond.
 template <int KMAX, int SUB, int MODE, int E>
 __device__ __forceinline__ void trial3(uint8_t* lat, int ai, const OwnCells& o, uint32_t u, uint64_t valid,
                                        const int32_t* wtab, const double* tab, float ln2kT, Sums& sums, Window& w)
@@ -274,7 +272,6 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, const OwnCells& o, 
     constexpr bool DIFF = DOT || Field<KMAX>::F == 5;
     constexpr int ex = E & 1, ey = (E >> 1) & 1, ez = (E >> 2) & 1;
     constexpr int dx = ex ? 1 : -1, dy = ey ? 1 : -1, dz = ez ? 1 : -1;
-    constexpr bool odd = (ex + ey + ez) & 1;
     uint32_t (&s1)[8] = SUB == 0 ? w.a : w.c;
     const uint32_t ci = SUB == 0 ? w.c[1] : w.a[7], cj = s1[E];
 
@@ -329,9 +326,13 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, const OwnCells& o, 
     // Cells of the window first, then the loaded ones in load order.
     constexpr uint32_t bias = kFieldBias<KMAX, DOT>;
     uint32_t hi[kMaxS], hj[kMaxS] = {0u, 0u, 0u};
-    // the site's first shell, indices of even / odd popcount
-    const uint32_t T0 = count4_from0(s1[0], s1[3], s1[5], s1[6]), T1 = count4_from0(s1[1], s1[2], s1[4], s1[7]);
-    hi[0] = T0 + T1 + bias;
+    // the site's first shell but the partner and the cell opposite to it, by
+    // the parity of the flipped direction bits: j's third- and second-shell
+    // cells among them
+    const uint32_t t_same = count3_from0(s1[E ^ 3], s1[E ^ 5], s1[E ^ 6]);
+    const uint32_t t_other = count3_from0(s1[E ^ 1], s1[E ^ 2], s1[E ^ 4]);
+    hi[0] = t_same + t_other + bias;
+    count2<false>(hi[0], cj, s1[E ^ 7]);
     // second and third shell: the plane sums of the window, the next plane's,
     // and the cells at dx = 0 of the third shell
     uint32_t (&mine)[2] = SUB == 0 ? w.pc : w.pb;
@@ -339,12 +340,8 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, const OwnCells& o, 
     const uint32_t next_plane = count4_from(bias, r3[0], r3[1], r3[4], r3[5]);
     hi[2] = count4_from(0u - bias, r3[8], r3[9], r3[10], r3[11]);
     hi[2] += mine[0] + next_plane;
-    hi[1] = mine[1];
-    count2<false>(hi[1], r2[1], r2[0]);
+    hi[1] = count2_onto(mine[1], r2[1], r2[0]);
     uint32_t (&h)[kMaxS] = DIFF ? hi : hj;   // j's counts: subtracted from i's in the difference form
-    uint32_t t_same = odd ? T1 : T0, t_other = odd ? T0 : T1;
-    count1<true>(t_same, cj);         // j's third-shell cells among the site's first shell
-    count1<true>(t_other, s1[E ^ 7]); // j's second-shell cells among them
     count4<DIFF>(h[0], ci, r2[ex ? 0 : 1], r2[ey ? 2 : 3], r2[ez ? 4 : 5]);
     count4<DIFF>(h[0], r3[(ex ? 0 : 2) + (ey ? 0 : 1)], r3[4 + (ex ? 0 : 2) + (ez ? 0 : 1)],
                  r3[8 + (ey ? 0 : 2) + (ez ? 0 : 1)], q0);
@@ -368,10 +365,8 @@ __device__ __forceinline__ void trial3(uint8_t* lat, int ai, const OwnCells& o, 
 
     // ---- the window of the next trial ----
     s1[E] = cj_new;
-    if constexpr (E == 2 || E == 3 || E == 4 || E == 5) {   // the partner is a cell of a plane sum
-        count1<false>(others[E & 1], cj_new);
-        count1<true>(others[E & 1], cj);
-    }
+    if constexpr (E == 2 || E == 3 || E == 4 || E == 5)   // the partner is a cell of a plane sum
+        others[E & 1] = count_swap(others[E & 1], cj_new, cj);
     mine[0] = mine[1];
     mine[1] = next_plane;
     if constexpr (SUB == 0) {
