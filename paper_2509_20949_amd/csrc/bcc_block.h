@@ -39,9 +39,8 @@ using WavePitch = BccPitch<kP, kPP, kArr>;
 //   corner: (z+1)*kPP + (y+1)*kP + (x+1)       x in -1..13
 //   body:   kArr + (z+2)*kPP + (y+2)*kP + (x+2) x in -2..12
 
-// Rows whose loads a lane issues together when staging a block (registers
-// bound it: one aligned word per row once the two loads are joined).
-constexpr int kStageBatch = 16;
+
+constexpr int kStageRows = 16;
 
 // Geometry of one block of colour `colour` in sweep s (wave-uniform).
 struct BccBlock {
@@ -149,16 +148,17 @@ __device__ __forceinline__ void bcc_base_cell(const BccBlock& B, uint32_t z_off,
 
 // Stage block + halo, HBM -> LDS codes (NW waves share the planes: wave w
 // takes planes -2 + w * 16 / NW onwards).  dot_codes: this lattice's rows of
-// weights are in the byte-dot form.  NW = 4: a wave's loads are one batch, and
-// `between` (work that needs no loaded byte) runs while they are in flight.
+// weights are in the byte-dot form.  `between` (work that needs no loaded
+// byte) runs while the loads are in flight.
 // (The launches that share a block have planes far below 2 GiB.)
 template <int KMAX, class LY, bool SLAB, int NW, class Fn>
 __device__ __forceinline__ void bcc_stage(const BccBlock& B, uint8_t* lat, int lane, int w, bool dot_codes, Fn&& between)
 {
     static_assert(NW == 1 || NW == 4, "waves per block");
     constexpr int F = Field<KMAX>::F;
-    constexpr int BATCH = kStageBatch < 32 / NW ? kStageBatch : 32 / NW;
-    const int lz0 = w * (16 / NW) - 2;
+    // Rows a lane has in flight at once (registers bound it: two words per row).
+    constexpr int ROWS = NW == 1 ? kStageRows : 32 / NW;
+    const int lz_first = w * (16 / NW) - 2;
     // species bytes -> LDS codes for this lattice's form of the weight rows
     auto encode = [&](uint32_t v) -> uint32_t {
         if constexpr (KMAX <= 5) {
@@ -179,6 +179,29 @@ __device__ __forceinline__ void bcc_stage(const BccBlock& B, uint8_t* lat, int l
     // register for the whole staging rather than copying it there per row
     asm volatile("" : "+v"(code_lo));
 
+    // Cells lx0, lx0 + 1 of the lane's rows (codes corner, body, corner, body
+    // in a word) into the image: row it is row h = it & 1 of plane lz0 + it / 2,
+    // corner(lx0, ly, -1) at cl[h] less a plane.  Each of the four bytes has a
+    // lane mask of its own, set once for all planes.
+    auto put = [&](int lz0, const uint32_t (&v)[ROWS], const int (&cl)[2], const bool (&mc0)[2], const bool (&mc1)[2],
+                   const bool (&mb0)[2], const bool (&mb1)[2]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint8_t* p0 = lat + cl[h] + (lz0 + 1) * LY::PP;      // corner(lx0, ly, lz0)
+            uint8_t* q0 = p0 + LY::kBodyFromCorner;
+            auto planes = [&](uint8_t* at, int shift, bool body) {
+#pragma unroll
+                for (int k = 0; k < ROWS / 2; ++k)
+                    if (body ? lz0 + k <= 12 : lz0 + k >= -1)   // (wave-uniform)
+                        at[k * LY::PP] = (uint8_t)(v[2 * k + h] >> shift);
+            };
+            if (mc0[h]) planes(p0, 0, false);
+            if (mc1[h]) planes(p0 + 1, 16, false);
+            if (mb0[h]) planes(q0, 8, true);
+            if (mb1[h]) planes(q0 + 1, 24, true);
+        }
+    };
+
     // ---- stage block + halo: local cells -2..w+1 on each axis ----
     // Fast path (the block's x-range does not cross the periodic boundary):
     // 8 lanes per row, each taking cells lx0, lx0 + 1 (lx0 = 2 (lane & 7) - 2),
@@ -188,7 +211,7 @@ __device__ __forceinline__ void bcc_stage(const BccBlock& B, uint8_t* lat, int l
     // plane lz = -2 .. 13.  Per lane, the in-plane byte offsets and LDS
     // positions of its two rows are set up once; a row adds only its plane,
     // which is wave-uniform (the buffer resource's base, scalar registers).
-    // All 16 loads of a batch are issued before any LDS write.  Rows, planes
+    // All its loads are issued before any LDS write.  Rows, planes
     // and cells past the halo (w < 12) load an in-range cell and write it to
     // image positions past w + 1, which no trial with a site and no
     // write-back reads; only positions outside the 15^3 arrays (corner -2,
@@ -214,34 +237,22 @@ __device__ __forceinline__ void bcc_stage(const BccBlock& B, uint8_t* lat, int l
             mb1[h] = ly <= 12 && c8 <= 6;
         }
 #pragma unroll
-        for (int it0 = 0; it0 < 32 / NW; it0 += BATCH) {
-            uint32_t v[BATCH];
+        for (int n = 0; n < 32 / NW / ROWS; ++n) {
+            const int lz0 = lz_first + n * (ROWS / 2);
+            uint32_t v[ROWS];
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int it = it0 + u, h = it & 1, lz = lz0 + (it >> 1);
+            for (int it = 0; it < ROWS; ++it) {
+                const int h = it & 1, lz = lz0 + (it >> 1);
                 const uint64_t zb = B.plane_bytes * (uint32_t)B.zplane<SLAB>(min(lz, B.wz + 1));
                 const uint64_t base = zb & ~(uint64_t)3;
                 const __amdgpu_buffer_rsrc_t r = byte_rsrc(B.g + base, B.buf_bytes - base);
                 const uint32_t at = yoff[h] + ((uint32_t)zb & 2u);
                 const uint32_t A = at & ~3u;
-                v[u] = __builtin_amdgcn_perm(code_hi, code_lo,
-                                             __builtin_amdgcn_alignbyte(bload32(r, A + 4), bload32(r, A), at));
+                v[it] = __builtin_amdgcn_perm(code_hi, code_lo,
+                                              __builtin_amdgcn_alignbyte(bload32(r, A + 4), bload32(r, A), at));
             }
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int it = it0 + u, h = it & 1, lz = lz0 + (it >> 1);
-                uint8_t* p = lat + cl[h] + (lz + 1) * LY::PP;   // corner(lx0, ly, lz)
-                uint8_t* q = p + LY::kBodyFromCorner;      // body(lx0, ly, lz)
-                const uint32_t w8 = v[u] >> 8;
-                if (lz >= -1) {
-                    if (mc0[h]) p[0] = (uint8_t)v[u];
-                    if (mc1[h]) p[1] = (uint8_t)(v[u] >> 16);
-                }
-                if (lz <= 12) {
-                    if (mb0[h]) q[0] = (uint8_t)w8;
-                    if (mb1[h]) q[1] = (uint8_t)(w8 >> 16);
-                }
-            }
+            if (n == 0) between();
+            put(lz0, v, cl, mc0, mc1, mb0, mb1);
         }
     } else if (NW > 1 || B.plane32) {
         // The x-range crosses the periodic boundary: the rows and LDS
@@ -270,46 +281,35 @@ __device__ __forceinline__ void bcc_stage(const BccBlock& B, uint8_t* lat, int l
             mb1[h] = ly <= 12 && c8 <= 6;
         }
 #pragma unroll
-        for (int it0 = 0; it0 < 32 / NW; it0 += BATCH) {
-            uint32_t v[BATCH], v2[BATCH];
+        for (int n = 0; n < 32 / NW / ROWS; ++n) {
+            const int lz0 = lz_first + n * (ROWS / 2);
+            uint32_t v[ROWS], v2[ROWS];
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int it = it0 + u, h = it & 1, lz = lz0 + (it >> 1);
+            for (int it = 0; it < ROWS; ++it) {
+                const int h = it & 1, lz = lz0 + (it >> 1);
                 const uint64_t zb = B.plane_bytes * (uint32_t)B.zplane<SLAB>(min(lz, B.wz + 1));
                 const uint64_t base = zb & ~(uint64_t)3;
                 const __amdgpu_buffer_rsrc_t r = byte_rsrc(B.g + base, B.buf_bytes - base);
                 const int so = (int)((uint32_t)zb & 2u);
-                v[u] = __builtin_amdgcn_raw_buffer_load_b16(r, (int)oa[h], so, 0);
-                v2[u] = __builtin_amdgcn_raw_buffer_load_b16(r, (int)ob[h], so, 0);
-                if constexpr (NW == 1) v[u] = __builtin_amdgcn_perm(code_hi, code_lo, v[u] | v2[u] << 16);
+                v[it] = __builtin_amdgcn_raw_buffer_load_b16(r, (int)oa[h], so, 0);
+                v2[it] = __builtin_amdgcn_raw_buffer_load_b16(r, (int)ob[h], so, 0);
             }
-            if constexpr (NW > 1) {
+            if (n == 0) {
                 __builtin_amdgcn_sched_barrier(0);
                 between();
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int it = it0 + u, h = it & 1, lz = lz0 + (it >> 1);
-                if constexpr (NW > 1) v[u] = __builtin_amdgcn_perm(code_hi, code_lo, v[u] | v2[u] << 16);
-                uint8_t* p = lat + cl[h] + (lz + 1) * LY::PP;
-                uint8_t* q = p + LY::kBodyFromCorner;
-                const uint32_t w8 = v[u] >> 8;
-                if (lz >= -1) {
-                    if (mc0[h]) p[0] = (uint8_t)v[u];
-                    if (mc1[h]) p[1] = (uint8_t)(v[u] >> 16);
-                }
-                if (lz <= 12) {
-                    if (mb0[h]) q[0] = (uint8_t)w8;
-                    if (mb1[h]) q[1] = (uint8_t)(w8 >> 16);
-                }
-            }
+            for (int it = 0; it < ROWS; ++it) v[it] = __builtin_amdgcn_perm(code_hi, code_lo, v[it] | v2[it] << 16);
+            put(lz0, v, cl, mc0, mc1, mb0, mb1);
         }
     } else if constexpr (NW == 1) {
         // planes of 2 GiB or more: one cell (two bytes) per lane, rows
         // r = (lane >> 4) + 4 it, 64-bit addresses; all 64 loads of a lane
         // are issued before any LDS write, as on the fast path (lanes and
         // rows outside the halo load a clamped in-range cell)
+        between();
+        constexpr int BATCH = 16;
         const int lx = (lane & 15) - 2;
         const bool okx = lx <= B.wx + 1;
         const int gx = wrap_add(B.gx0 + (okx ? lx : -2), B.Lx);
@@ -340,7 +340,7 @@ __device__ __forceinline__ void bcc_stage(const BccBlock& B, uint8_t* lat, int l
 }
 
 // Write the block and its first-neighbour ring back (wave w takes every
-// NW-th plane).
+// NW-th pair of planes).
 template <class LY, bool SLAB, int NW>
 __device__ __forceinline__ void bcc_write_back(const BccBlock& B, const uint8_t* lat, int lane, int w)
 {
@@ -358,7 +358,8 @@ __device__ __forceinline__ void bcc_write_back(const BccBlock& B, const uint8_t*
     // instruction: lane row lys = lane >> 4 takes rows ly = 4 yg + lys - 1
     // (yg = 0..3) of each plane lz = -1..w.  Per lane, the in-plane byte
     // offsets and LDS positions of its four rows are set up once; lanes past
-    // the box read a clamped in-image cell and store nothing.  A lane's x is
+    // the box read a clamped in-image cell and store past the plane, which the
+    // resource's bound drops.  A lane's x is
     // wrapped once here, so blocks whose x-range crosses the periodic
     // boundary take this path too (same-colour blocks are as far apart
     // across the boundary as anywhere else, nb being even).
@@ -367,30 +368,36 @@ __device__ __forceinline__ void bcc_write_back(const BccBlock& B, const uint8_t*
         const int lxc = min(lx, B.wx);
         uint32_t yo[4];
         int cw[4];
-        bool ok[4];
 #pragma unroll
         for (int yg = 0; yg < 4; ++yg) {
             const int ly = 4 * yg + lys - 1, lyc = min(ly, B.wy);
-            ok[yg] = lx <= B.wx && ly <= B.wy;
             const uint32_t gy = (uint32_t)wrap_add(B.gy0 + lyc, B.Ly);
-            yo[yg] = 2u * (gy * (uint32_t)B.Lx + (uint32_t)wrap_add(B.gx0 + lxc, B.Lx));
+            const uint32_t at = 2u * (gy * (uint32_t)B.Lx + (uint32_t)wrap_add(B.gx0 + lxc, B.Lx));
+            yo[yg] = lx <= B.wx && ly <= B.wy ? at : 1u << 31;   // past the plane: the store is dropped
             cw[yg] = (lyc + 1) * LY::P + (lxc + 1);   // corner(lxc, lyc, -1), less a plane
         }
+        // two planes at a time: their LDS reads are issued together (the
+        // second of an odd last pair is the first again)
+        constexpr int PAIRS = (kMaxBlock + 2 + 2 * NW - 1) / (2 * NW);
 #pragma unroll
-        for (int k = 0; k < (kMaxBlock + 2 + NW - 1) / NW; ++k) {
-            const int lz = NW * k + w - 1;
-            if (lz > B.wz) continue;   // (wave-uniform)
-            const uint64_t zb = B.plane_bytes * (uint32_t)B.zplane<SLAB>(lz);
-            const __amdgpu_buffer_rsrc_t r = byte_rsrc(B.g + zb, B.buf_bytes - zb);
-            uint32_t e[4];
+        for (int k = 0; k < PAIRS; ++k) {
+            const int lz0 = 2 * (NW * k + w) - 1;
+            if (lz0 > B.wz) continue;   // (wave-uniform)
+            uint32_t e[2][4];
 #pragma unroll
-            for (int yg = 0; yg < 4; ++yg) {
-                const uint8_t* p = lat + cw[yg] + (lz + 1) * LY::PP;   // corner(lxc, lyc, lz)
-                e[yg] = (uint32_t)p[0] | (uint32_t)p[LY::kBodyFromCorner] << 8;
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int yg = 0; yg < 4; ++yg) {
+                    const uint8_t* p = lat + cw[yg] + (min(lz0 + n, B.wz) + 1) * LY::PP;   // corner(lxc, lyc, lz)
+                    e[n][yg] = (uint32_t)p[0] | (uint32_t)p[LY::kBodyFromCorner] << 8;
+                }
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                const uint64_t zb = B.plane_bytes * (uint32_t)B.zplane<SLAB>(min(lz0 + n, B.wz));
+                const __amdgpu_buffer_rsrc_t r = byte_rsrc(B.g + zb, B.plane_bytes);
+#pragma unroll
+                for (int yg = 0; yg < 4; ++yg) bstore16(r, yo[yg], (e[n][yg] >> 5) & 0x0707u);
             }
-#pragma unroll
-            for (int yg = 0; yg < 4; ++yg)
-                if (ok[yg]) bstore16(r, yo[yg], (e[yg] >> 5) & 0x0707u);
         }
     } else if constexpr (NW == 1) {
         // planes of 2 GiB or more: one cell (two bytes) per lane, rows

@@ -507,24 +507,39 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     const DevLattice& D = lats[li];
     const uint32_t s = D.sweep0 + (uint32_t)t;
 
-    // Weight planes in LDS; the threshold tables of sweep s stay in global
-    // memory (read only for the few draws whose decision needs them), which
-    // leaves LDS for five workgroups per CU.
-    load_wplanes<KMAX, SMAX, kPlane>(s_w, D.wtab);
-    __syncthreads();
+    // The words of the weight planes, on their way while the block is set up.
+    // The threshold tables of sweep s stay in global memory (read only for the
+    // few draws whose decision needs them), which leaves LDS for five
+    // workgroups per CU.
+    constexpr int kWords = wplanes(KMAX, SMAX) * kPlane, kWPer = (kWords + kWave * WPG - 1) / (kWave * WPG);
+    int32_t wword[kWPer];
+#pragma unroll
+    for (int n = 0; n < kWPer; ++n) {
+        const int k = n * kWave * WPG + (int)threadIdx.x, row = k % kPlane;
+        wword[n] = k < kWords && row < KMAX * KMAX ? D.wtab[row * wrow(KMAX, SMAX) + k / kPlane] : 0;
+    }
     int ti = (int)(s - D.tab_s0);
     ti = ti < 0 ? 0 : (ti >= D.n_tabs ? D.n_tabs - 1 : ti);
     const double* g_tab = D.tabs + (size_t)ti * kTab;
 
     f += wave;
-    if (f >= D.blocks_per_colour) return;   // no later barrier
-
+    const bool active = f < D.blocks_per_colour;   // wave-uniform; the group's last waves may have no block
     const uint32_t k0 = D.key[0], k1 = D.key[1];
     const BccDraws pb = bcc_draws(s, colour, k0, k1, lane);
-    const BccBlock B = bcc_block<SLAB>(D, f, s, colour, pb);
+    const BccBlock B = bcc_block<SLAB>(D, active ? f : 0, s, colour, pb);
     uint8_t* lat = s_lat + wave * kWaveLds;
     const bool dot_codes = KMAX <= 5 && D.drop_last == kWtabDot;
-    bcc_stage<KMAX, WavePitch, SLAB, 1>(B, lat, lane, 0, dot_codes, [] {});
+    auto put_weights = [&] {
+#pragma unroll
+        for (int n = 0; n < kWPer; ++n) {
+            const int k = n * kWave * WPG + (int)threadIdx.x;
+            if (k < kWords) s_w[k] = wword[n];
+        }
+    };
+    if (active) bcc_stage<KMAX, WavePitch, SLAB, 1>(B, lat, lane, 0, dot_codes, put_weights);
+    else put_weights();
+    __syncthreads();
+    if (!active) return;   // no later barrier
 
     // ---- 27 residue classes x 2 sublattices = 54 rounds ----
     // Lane (ix, iy, iz) takes local cell (rx + 3 ix, ry + 3 iy, rz + 3 iz) of
