@@ -229,6 +229,48 @@ __device__ __forceinline__ void accept_bounds(uint32_t u, float c, int& lo, int&
     hi = (int)fminf(ehi, 1.0e9f);
 }
 
+// The Metropolis test of Eq. (3) for the draw u as two edges on float(dE):
+// dE <= lo is accepted and dE > hi rejected without the tables.  From e as in
+// accept_edges (device_common.h): hi = e + 8; lo = e - 8, but at least 0, so
+// that dE <= 0 passes, and at most the lower edge of u = 1, which u = 0 (e =
+// +inf, its upper edge too) passes as well.
+struct Edges {
+    float lo, hi;
+};
+__device__ __forceinline__ Edges edges_of(uint32_t u, float ln2kT)
+{
+    Edges x;
+    accept_edges(u, ln2kT, x.lo, x.hi);
+    x.lo = __builtin_amdgcn_fmed3f(x.lo, 0.0f, 32.0f * ln2kT - kAcceptMargin);
+    return x;
+}
+
+// The lanes (a mask) whose trial accepts dE: the exact test on the FP64 byte
+// tables (global memory, L2-resident) only where a lane with a site lies
+// between its edges, a few percent of the rounds.  The masks live in scalar
+// registers.
+__device__ __forceinline__ uint64_t accepted_lanes(int32_t dE, uint32_t u, const Edges& x, uint64_t valid,
+                                                   const double* tab)
+{
+    const float f = (float)dE;   // exact below 2^24; both edges of a draw u > 0 lie below 2^24
+    uint64_t sure = __builtin_amdgcn_ballot_w64(f <= x.lo) & valid;
+    const uint64_t near = __builtin_amdgcn_ballot_w64(f <= x.hi) & valid & ~sure;
+    if (__builtin_expect(near != 0, 0)) {
+        const int e = dE < 1 ? 1 : (dE > (1 << 24) - 1 ? (1 << 24) - 1 : dE);
+        const uint8_t* tb = (const uint8_t*)tab;
+        const double thr = (gload<double>(tb + 8 * (512 + (e >> 16))) * gload<double>(tb + 8 * (256 + ((e >> 8) & 255)))) *
+                           gload<double>(tb + 8 * (e & 255));
+        sure |= __builtin_amdgcn_ballot_w64((dE < (1 << 24)) & ((double)u < thr)) & near;
+    }
+    return sure;
+}
+
+// What a wave's trials add up.
+struct Sums {
+    int32_t dE;      // of the current class (two changes below 2^29 each)
+    uint32_t nacc;   // accepted swaps of the wave: wave-uniform, counted on the scalar unit
+};
+
 // XCD-aware workgroup order of a sweep launch.  Workgroups are
 // handed to the 8 XCDs of the chip in turn (workgroup b to XCD b % 8), each
 // XCD with its own L2.  Workgroup b therefore takes group

@@ -17,6 +17,8 @@
 // offset.  A trial's own draw is its acceptance word: one Philox call per
 // cell serves the cell's four sites.  (The FCC pair counts are in
 // pair_counts.hip.)
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace smcx {
@@ -31,8 +33,7 @@ constexpr int SH3[24][3] = {{+2, +1, +1}, {+2, +1, -1}, {+2, -1, +1}, {+2, -1, -
                             {+1, -2, +1}, {+1, -2, -1}, {-1, -2, +1}, {-1, -2, -1}, {+1, +1, +2}, {+1, -1, +2},
                             {-1, +1, +2}, {-1, -1, +2}, {+1, +1, -2}, {+1, -1, -2}, {-1, +1, -2}, {-1, -1, -2}};
 constexpr int kArrays = 4;
-constexpr int kBpOff = kArrays * kArr;      // per-wave partner-sublattice table (108 bytes)
-constexpr int kWaveLdsF = kBpOff + 112;
+constexpr int kWaveLdsF = kArrays * kArr;
 
 constexpr int origin(int b, int a) { return 1 + SUB[b][a]; }
 constexpr int stride(int a) { return a == 0 ? 1 : (a == 1 ? kP : kPP); }
@@ -134,45 +135,119 @@ constexpr int F = 6;
 constexpr int KMAXF = 5;
 constexpr uint32_t kBias = 32u * (1u | 1u << 6 | 1u << 12 | 1u << 18 | 1u << 24);
 
-// One trial: site at LDS byte ai (sublattice B), partner in sublattice BP
-// with the signs SG (bit 0: first differing axis, bit 1: second; set = +1),
-// all three wave-uniform, acceptance draw u_acc.
-// mode: the form of the weight rows (wave-uniform): kWtabDot or kWtabFull.
-template <int SMAX, int B, int BP, int SG>
-__device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u_acc, bool valid, int mode,
-                                      const int32_t* wtab, const double* tab, float ln2kT, int64_t& dEsum,
-                                      uint32_t& nacc)
+// The cells of a trial in the order it counts them: those that count in shell
+// s with sign + or - as lists of cell indices, and the loads that no earlier
+// list has asked for.
+struct CountLists {
+    int n[kMaxS][2];
+    int cell[kMaxS][2][32];
+    int n_load;
+    int load[64];   // cells in load order: site, partner, then as counted
+};
+template <int S> constexpr CountLists make_lists(const DiffCells& c)
 {
-    int e_lo, e_hi;
-    accept_bounds(u_acc, ln2kT, e_lo, e_hi);   // depends on the draw only
-    constexpr int PS = wplane(KMAXF);
-    constexpr DiffCells C = Diff<B, BP, SG, SMAX>::v;
-    static_assert(C.n <= 64 && C.i_site >= 0 && C.i_partner >= 0, "cell table");
-    // packed per-shell fields bias + n_i - n_j over the symmetric
-    // differences (6-bit fields, or bytes in the byte-dot form), with the
-    // codes of the site and of the partner
-    uint32_t h[kMaxS];
-#pragma unroll
-    for (int s = 0; s < kMaxS; ++s) h[s] = mode == kWtabDot ? 0x20202020u : kBias;
-    uint32_t ci = 0u, cj = 0u;
-#pragma unroll
-    for (int k = 0; k < C.n; ++k) {
-        const uint32_t c = lat[ai + C.off[k]];
-        if (k == C.i_site) ci = c;
-        if (k == C.i_partner) cj = c;
-#pragma unroll
-        for (int s = 0; s < SMAX; ++s) {
-            if (C.plus[k] >> s & 1) count1<false>(h[s], c);
-            if (C.minus[k] >> s & 1) count1<true>(h[s], c);
+    CountLists l{};
+    bool seen[64] = {};
+    l.load[l.n_load++] = c.i_site;
+    l.load[l.n_load++] = c.i_partner;
+    seen[c.i_site] = seen[c.i_partner] = true;
+    for (int s = 0; s < S; ++s)
+        for (int sign = 0; sign < 2; ++sign)
+            for (int k = 0; k < c.n; ++k)
+                if ((sign ? c.minus[k] : c.plus[k]) >> s & 1) {
+                    l.cell[s][sign][l.n[s][sign]++] = k;
+                    if (!seen[k]) {
+                        seen[k] = true;
+                        l.load[l.n_load++] = k;
+                    }
+                }
+    return l;
+}
+template <int B, int BP, int SG, int S> struct Lists {
+    static constexpr DiffCells cells = Diff<B, BP, SG, S>::v;
+    static constexpr CountLists v = make_lists<S>(cells);
+};
+
+// Loads From .. To - 1 of the load order into c.
+template <class L, int From, int To>
+__device__ __forceinline__ void load_cells(uint32_t (&c)[64], const uint8_t* lat, int ai)
+{
+    if constexpr (From < To) {
+        constexpr int k = L::v.load[From], off = L::cells.off[k];
+        c[k] = lat[ai + off];
+        load_cells<L, From + 1, To>(c, lat, ai);
+    }
+}
+
+// Counts entries At .. of list (s, sign) into h, four to an asm block.
+template <class L, int s, int sign, int At = 0>
+__device__ __forceinline__ void count_list(uint32_t& h, const uint32_t (&c)[64])
+{
+    constexpr int left = L::v.n[s][sign] - At;
+    if constexpr (left > 0) {
+        constexpr const int* list = L::v.cell[s][sign];
+        constexpr int k0 = list[At], k1 = list[At + (left > 1)], k2 = list[At + 2 * (left > 2)],
+                      k3 = list[At + 3 * (left > 3)];
+        if constexpr (left >= 4) {
+            count4<sign == 1>(h, c[k0], c[k1], c[k2], c[k3]);
+            count_list<L, s, sign, At + 4>(h, c);
+        } else if constexpr (left == 3) {
+            count3<sign == 1>(h, c[k0], c[k1], c[k2]);
+        } else if constexpr (left == 2) {
+            count2<sign == 1>(h, c[k0], c[k1]);
+        } else {
+            count1<sign == 1>(h, c[k0]);
         }
     }
-    const int aj = ai + C.off_partner;
-    const uint32_t a = min(decode(ci), (uint32_t)(KMAXF - 1)), b = min(decode(cj), (uint32_t)(KMAXF - 1));
-    const int32_t* w = wtab + (a * KMAXF + b);   // row (a, b) of the weight planes
-    // (kmax = 5: the table builder gives the byte-dot rows or, when the
-    // weights are too large for them, full rows of KMAXF fields per shell)
+}
+
+// One trial: site at LDS byte ai (sublattice B), partner in sublattice BP
+// with the signs SG (bit 0: first differing axis, bit 1: second; set = +1),
+// all three wave-uniform, acceptance draw u.  MODE: the form of the weight
+// rows (per lattice): kWtabDot or kWtabFull.
+// The site's and the partner's codes are loaded first, so that their weight
+// row is requested while the other cells are still arriving; every load is
+// issued before the first count.
+template <int SMAX, int MODE, int B, int BP, int SG>
+__device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, uint64_t valid, const int32_t* wtab,
+                                      const double* tab, float ln2kT, Sums& sums)
+{
+    constexpr bool DOT = MODE == kWtabDot;
+    using L = Lists<B, BP, SG, SMAX>;
+    constexpr DiffCells C = L::cells;
+    static_assert(C.n <= 64 && C.i_site >= 0 && C.i_partner >= 0 && L::v.n_load == C.n, "cell table");
+    constexpr int kAhead = C.n < 14 ? C.n : 14;   // (the LDS counter tells at most 15 loads in flight apart)
+    uint32_t c[64];
+    load_cells<L, 0, kAhead>(c, lat, ai);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t ci = c[C.i_site], cj = c[C.i_partner];
+    // row (a, b) of the weight planes at byte 4 (5 a + b) of a plane
+    const uint32_t row4 = __umul24(ci >> 5, 4u * KMAXF) + ((cj >> 5) << 2);
+    const int32_t* w = (const int32_t*)((const uint8_t*)wtab + row4);
+    constexpr int NW = DOT ? 3 * SMAX + 1 : 1;
+    int32_t row[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) row[k] = w[(DOT ? k : SMAX * KMAXF) * kPlane];
+    load_cells<L, kAhead, C.n>(c, lat, ai);
+    __builtin_amdgcn_sched_barrier(0);
+    const Edges edges = edges_of(u, ln2kT);   // depends on the draw only
+    // packed per-shell fields bias + n_i - n_j over the symmetric
+    // differences (6-bit fields, or bytes in the byte-dot form)
+    uint32_t h[kMaxS];
+#pragma unroll
+    for (int s = 0; s < kMaxS; ++s) h[s] = DOT ? 0x20202020u : kBias;
+    count_list<L, 0, 0>(h[0], c);
+    count_list<L, 0, 1>(h[0], c);
+    if constexpr (SMAX >= 2) {
+        count_list<L, 1, 0>(h[1], c);
+        count_list<L, 1, 1>(h[1], c);
+    }
+    if constexpr (SMAX >= 3) {
+        count_list<L, 2, 0>(h[2], c);
+        count_list<L, 2, 1>(h[2], c);
+    }
     uint32_t acc;
-    if (mode == kWtabDot) {
+    if constexpr (DOT) {
         // bytes 32 + n_i - n_j (bit 31, the last species, masked off) dotted
         // with the three base-256 digits of the folded weights, in one
         // chain: ((A2 * 256 + A1) * 256 + constant) + A0
@@ -181,68 +256,62 @@ __device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u_acc, bool
         for (int s = 0; s < SMAX; ++s) dd[s] = (int32_t)(h[s] & 0x7fffffffu);
         int32_t X = 0;
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(dd[s], w[(3 * s + 2) * PS], X, false);
+        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(dd[s], row[3 * s + 2], X, false);
         X = (int32_t)((uint32_t)X << 8);
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(dd[s], w[(3 * s + 1) * PS], X, false);
-        X = (int32_t)(((uint32_t)X << 8) + (uint32_t)w[3 * SMAX * PS]);
+        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(dd[s], row[3 * s + 1], X, false);
+        X = (int32_t)(((uint32_t)X << 8) + (uint32_t)row[3 * SMAX]);
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(dd[s], w[(3 * s + 0) * PS], X, false);
+        for (int s = 0; s < SMAX; ++s) X = __builtin_amdgcn_sdot4(dd[s], row[3 * s], X, false);
         acc = (uint32_t)X;
     } else {
-        acc = (uint32_t)w[SMAX * KMAXF * PS];
+        acc = (uint32_t)row[0];
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) {
 #pragma unroll
-            for (int p = 0; p < KMAXF; ++p) acc = mad24((h[s] >> (F * p)) & 63u, w[(s * KMAXF + p) * PS], acc);
+            for (int p = 0; p < KMAXF; ++p) acc = mad24((h[s] >> (F * p)) & 63u, w[(s * KMAXF + p) * kPlane], acc);
         }
     }
     const int32_t dE = (int32_t)acc;
-    // Metropolis decision, Eq. (3): the exact table test (tables in global
-    // memory) only for lanes between their bounds
-    const bool up = (dE > 0) & (dE < (1 << 24));
-    const bool near = up & (((dE > e_lo) & (dE <= e_hi)) | (u_acc == 0u));
-    bool up_ok = up & (dE <= e_lo);
-    if (__builtin_amdgcn_ballot_w64(near)) {
-        const int e = dE < 1 ? 1 : (dE > (1 << 24) - 1 ? (1 << 24) - 1 : dE);
-        const uint8_t* tb = (const uint8_t*)tab;
-        const double thr = (gload<double>(tb + 8 * (512 + (e >> 16))) * gload<double>(tb + 8 * (256 + ((e >> 8) & 255)))) *
-                           gload<double>(tb + 8 * (e & 255));
-        up_ok = near ? (double)u_acc < thr : up_ok;
-    }
-    const bool accept = valid & (ci != cj) & ((dE <= 0) | up_ok);
+    const uint64_t ok = accepted_lanes(dE, u, edges, valid, tab);
     // both bytes stored by every lane (unchanged unless accepted): no two
     // lanes of a round touch the same byte
+    const bool accept = __builtin_amdgcn_inverse_ballot_w64(ok);
     lat[ai] = (uint8_t)(accept ? cj : ci);
-    lat[aj] = (uint8_t)(accept ? ci : cj);
-    dEsum += (int64_t)(accept ? dE : 0);
-    nacc += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(accept));   // wave-uniform
+    lat[ai + C.off_partner] = (uint8_t)(accept ? ci : cj);
+    sums.dE += accept ? dE : 0;   // (0 for equal species: their row is zero)
+    sums.nacc += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ci != cj) & ok);
 }
 
-// The partner sublattice BP and signs (wave-uniform values) select one
-// instantiation.
-template <int SMAX, int B, int BP>
-__device__ __forceinline__ void trial_signs(int signs, uint8_t* lat, int ai, uint32_t u_acc, bool valid, int drop,
-                                            const int32_t* wtab, const double* tab, float ln2kT, int64_t& dEsum,
-                                            uint32_t& nacc)
+// The trial of one of twelve partners (wave-uniform: index k of the partner
+// sublattice among those other than B in bits 2 and 3, signs in bits 0 and 1).
+// Tests of k, then of the signs, one after the other, each a compare and a
+// branch over the code it guards: as a switch the compiler makes every level
+// of the tree a chain of flags and branches (21 branches and 65 scalar
+// instructions a trial).  The empty asm keeps it from threading the tests
+// together again.
+template <int SMAX, int MODE, int B, int K>
+__device__ __forceinline__ void trial_signs(int p, uint8_t* lat, int ai, uint32_t u, uint64_t valid,
+                                            const int32_t* wtab, const double* tab, float ln2kT, Sums& sums)
 {
-    switch (signs) {
-    case 0: trial<SMAX, B, BP, 0>(lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); break;
-    case 1: trial<SMAX, B, BP, 1>(lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); break;
-    case 2: trial<SMAX, B, BP, 2>(lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); break;
-    default: trial<SMAX, B, BP, 3>(lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); break;
-    }
+    constexpr int BP = K + (K >= B ? 1 : 0);
+    if (p == 4 * K) trial<SMAX, MODE, B, BP, 0>(lat, ai, u, valid, wtab, tab, ln2kT, sums);
+    asm volatile("" : "+s"(p));
+    if (p == 4 * K + 1) trial<SMAX, MODE, B, BP, 1>(lat, ai, u, valid, wtab, tab, ln2kT, sums);
+    asm volatile("" : "+s"(p));
+    if (p == 4 * K + 2) trial<SMAX, MODE, B, BP, 2>(lat, ai, u, valid, wtab, tab, ln2kT, sums);
+    asm volatile("" : "+s"(p));
+    if (p == 4 * K + 3) trial<SMAX, MODE, B, BP, 3>(lat, ai, u, valid, wtab, tab, ln2kT, sums);
 }
-
-template <int SMAX, int B>
-__device__ __forceinline__ void trial_any(int bp, uint8_t* lat, int ai, int signs, uint32_t u_acc, bool valid, int drop,
-                                          const int32_t* wtab, const double* tab, float ln2kT, int64_t& dEsum,
-                                          uint32_t& nacc)
+template <int SMAX, int MODE, int B>
+__device__ __forceinline__ void trial_any(int p, uint8_t* lat, int ai, uint32_t u, uint64_t valid, const int32_t* wtab,
+                                          const double* tab, float ln2kT, Sums& sums)
 {
-    if constexpr (B != 0) { if (bp == 0) { trial_signs<SMAX, B, 0>(signs, lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); return; } }
-    if constexpr (B != 1) { if (bp == 1) { trial_signs<SMAX, B, 1>(signs, lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); return; } }
-    if constexpr (B != 2) { if (bp == 2) { trial_signs<SMAX, B, 2>(signs, lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); return; } }
-    if constexpr (B != 3) { if (bp == 3) { trial_signs<SMAX, B, 3>(signs, lat, ai, u_acc, valid, drop, wtab, tab, ln2kT, dEsum, nacc); return; } }
+    if (p < 4) trial_signs<SMAX, MODE, B, 0>(p, lat, ai, u, valid, wtab, tab, ln2kT, sums);
+    asm volatile("" : "+s"(p));
+    if ((p & 12) == 4) trial_signs<SMAX, MODE, B, 1>(p, lat, ai, u, valid, wtab, tab, ln2kT, sums);
+    asm volatile("" : "+s"(p));
+    if (p >= 8) trial_signs<SMAX, MODE, B, 2>(p, lat, ai, u, valid, wtab, tab, ln2kT, sums);
 }
 
 template <int B>
@@ -283,8 +352,12 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
                             int t, int colour)
 {
     using namespace fcc;
-    __shared__ int32_t s_w[wplanes(KMAXF, SMAX) * wplane(KMAXF)];
-    __shared__ __attribute__((aligned(16))) uint8_t s_lat[WPG * kWaveLdsF];
+    // the weight planes at LDS offset 0 (row addresses need no base), then
+    // the block images
+    constexpr int kWords = wplanes(KMAXF, SMAX) * kPlane, kWPer = (kWords + kWave * WPG - 1) / (kWave * WPG);
+    __shared__ __attribute__((aligned(16))) uint8_t s_mem[4 * kWords + WPG * kWaveLdsF];
+    int32_t* s_w = (int32_t*)s_mem;
+    uint8_t* s_lat = s_mem + 4 * kWords;
 
     const int wave = wave_id();
     const int lane = threadIdx.x % kWave;
@@ -299,23 +372,45 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
     }
     const DevLattice& D = lats[li];
     const uint32_t s = D.sweep0 + (uint32_t)t;
-    // weight planes in LDS; the threshold tables stay in global memory
-    load_wplanes<KMAXF, SMAX>(s_w, D.wtab);
-    __syncthreads();
+    // the words of the weight planes, on their way while the block is set up;
+    // the threshold tables stay in global memory
+    int32_t wword[kWPer];
+#pragma unroll
+    for (int n = 0; n < kWPer; ++n) {
+        const int k = n * kWave * WPG + (int)threadIdx.x, row = k % kPlane;
+        wword[n] = k < kWords && row < KMAXF * KMAXF ? D.wtab[row * wrow(KMAXF, SMAX) + k / kPlane] : 0;
+    }
     int ti = (int)(s - D.tab_s0);
     ti = ti < 0 ? 0 : (ti >= D.n_tabs ? D.n_tabs - 1 : ti);
     const double* g_tab = D.tabs + (size_t)ti * kTab;
     const float ln2kT = (float)g_tab[kTabLn2kT];
     f += wave;
-    if (f >= D.blocks_per_colour) return;   // no later barrier
+    const bool active = f < D.blocks_per_colour;   // wave-uniform; the group's last waves may have no block
+    if (!active) f = 0;
 
     const int hx = D.nb[0] >> 1, hy = D.nb[1] >> 1;
     const int kx = 2 * (f % hx) + (colour & 1);
     const int ky = 2 * ((f / hx) % hy) + ((colour >> 1) & 1);
     const int kz = 2 * (f / (hx * hy)) + ((colour >> 2) & 1);
     const int Lx = D.L[0], Ly = D.L[1], Lz = D.L[2];
-    uint32_t sh[4] = {0u, 0u, s, 8u};
-    philox4x32_10(sh, D.key[0], D.key[1]);
+    const uint32_t k0 = D.key[0], k1 = D.key[1];
+    // partner of every (colour, sub-colour q) set of this sweep, from
+    // r = Philox(key, (q, 0, s, c + 64)): sublattice = the k-th other than
+    // the set's own, k = (r0 * 3) >> 32 (bits 2 and 3), signs = bits 30 and 31
+    // of r1 (bits 0 and 1).  Lane q (q - 64) of part[0] (part[1]) holds it;
+    // the origin shift (0, 0, s, 8) takes an idle lane of the second call.
+    int part[2];
+    uint32_t sh[3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int q = 64 * h + lane;
+        const bool own_shift = h == 1 && lane == 63;
+        uint32_t r[4] = {own_shift ? 0u : (uint32_t)q, 0u, s, own_shift ? 8u : (uint32_t)colour + 64u};
+        philox4x32_10(r, k0, k1);
+        if (h == 1)
+            for (int a = 0; a < 3; ++a) sh[a] = (uint32_t)__builtin_amdgcn_readlane((int)r[a], 63);
+        part[h] = (int)(((uint64_t)r[0] * 3u) >> 32) << 2 | (int)(r[1] >> 30);
+    }
     const int ox = (int)(((uint64_t)sh[0] * (uint32_t)Lx) >> 32);
     const int oy = (int)(((uint64_t)sh[1] * (uint32_t)Ly) >> 32);
     const int oz = (int)(((uint64_t)sh[2] * (uint32_t)Lz) >> 32);
@@ -323,27 +418,15 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
     const int y0 = block_lo(ky, Ly, D.nb[1]), wy = block_lo(ky + 1, Ly, D.nb[1]) - y0;
     const int z0 = block_lo(kz, Lz, D.nb[2]), wz = block_lo(kz + 1, Lz, D.nb[2]) - z0;
     const int gx0 = wrap_add(x0 + ox, Lx), gy0 = wrap_add(y0 + oy, Ly), gz0 = wrap_add(z0 + oz, Lz);
-    const uint32_t k0 = D.key[0], k1 = D.key[1];
 
     uint8_t* lat = s_lat + wave * kWaveLdsF;
     uint8_t* __restrict__ g = D.species;
-
-    // partner of every (colour, sub-colour q) set of this sweep, from
-    // r = Philox(key, (q, 0, s, c + 64)): sublattice = the k-th other than
-    // the set's own, k = (r0 * 3) >> 32 (low 2 bits of the byte), signs =
-    // bits 30 and 31 of r1 (bits 2 and 3)
-    for (int q = lane; q < 108; q += kWave) {
-        uint32_t r[4] = {(uint32_t)q, 0u, s, (uint32_t)colour + 64u};
-        philox4x32_10(r, k0, k1);
-        const int b = q & 3, k = (int)(((uint64_t)r[0] * 3u) >> 32);
-        lat[kBpOff + q] = (uint8_t)((k + (k >= b ? 1 : 0)) | (int)(r[1] >> 30) << 2);
-    }
 
     const bool dot_codes = D.drop_last == kWtabDot;   // LDS codes for the byte-dot weight rows
     // ---- stage block + halo: one cell (4 sublattice bytes, one dword) per lane ----
     // Rows r = (lane >> 4) + 4 it; the loads of 16 rows are issued together
     // (lanes and rows outside the halo load a clamped in-range cell).
-    {
+    if (active) {
         const int lx = (lane & 15) - 2;
         const bool okx = lx <= wx + 1;
         const int gx = wrap_add(gx0 + (okx ? lx : -2), Lx);
@@ -370,6 +453,14 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
         }
     }
 
+#pragma unroll
+    for (int n = 0; n < kWPer; ++n) {
+        const int k = n * kWave * WPG + (int)threadIdx.x;
+        if (k < kWords) s_w[k] = wword[n];
+    }
+    __syncthreads();
+    if (!active) return;   // no later barrier
+
     // ---- 27 residue classes x 4 sublattices = 108 rounds ----
     int ix, iy, iz;
     lane_cell(lane, ix, iy, iz);
@@ -377,38 +468,50 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
     const uint32_t LxLy = (uint32_t)Lx * (uint32_t)Ly;
     const bool narrow = LxLy < (1u << 24) && (uint64_t)LxLy * (uint32_t)Lz < (1ull << 32);
     int64_t dEsum = 0;
-    uint32_t nacc = 0;
-    const int drop = D.drop_last;   // the form of the weight rows
-    for (int m = 0; m < 27; ++m) {
-        const int rx = m % 3, ry = (m / 3) % 3, rz = m / 9;
-        const int lx = rx + 3 * ix, ly = ry + 3 * iy, lz = rz + 3 * iz;
-        const bool valid = (lx < wx) & (ly < wy) & (lz < wz);
-        uint32_t gx = bx + rx, gy = by + ry, gz = bz + rz;
-        gx = min(gx, gx - (uint32_t)Lx);
-        gy = min(gy, gy - (uint32_t)Ly);
-        gz = min(gz, gz - (uint32_t)Lz);
-        uint64_t cell;
-        if (narrow)
-            cell = __umul24(gz, LxLy) + __umul24(gy, (uint32_t)Lx) + gx;
-        else
-            cell = ((uint64_t)gz * (uint32_t)Ly + gy) * (uint32_t)Lx + gx;
-        // one Philox call per cell: site b accepts with word b
-        uint32_t ra[4] = {(uint32_t)cell, (uint32_t)(cell >> 32), s, (uint32_t)colour};
-        philox4x32_10(ra, k0, k1);
-        const int q0 = 4 * m;
-        int pb = __builtin_amdgcn_readfirstlane(lat[kBpOff + q0]);
-        trial_any<SMAX, 0>(pb & 3, lat, site_addr<0>(lx, ly, lz), pb >> 2, ra[0], valid, drop, s_w, g_tab, ln2kT, dEsum, nacc);
-        __builtin_amdgcn_wave_barrier();
-        pb = __builtin_amdgcn_readfirstlane(lat[kBpOff + q0 + 1]);
-        trial_any<SMAX, 1>(pb & 3, lat, site_addr<1>(lx, ly, lz), pb >> 2, ra[1], valid, drop, s_w, g_tab, ln2kT, dEsum, nacc);
-        __builtin_amdgcn_wave_barrier();
-        pb = __builtin_amdgcn_readfirstlane(lat[kBpOff + q0 + 2]);
-        trial_any<SMAX, 2>(pb & 3, lat, site_addr<2>(lx, ly, lz), pb >> 2, ra[2], valid, drop, s_w, g_tab, ln2kT, dEsum, nacc);
-        __builtin_amdgcn_wave_barrier();
-        pb = __builtin_amdgcn_readfirstlane(lat[kBpOff + q0 + 3]);
-        trial_any<SMAX, 3>(pb & 3, lat, site_addr<3>(lx, ly, lz), pb >> 2, ra[3], valid, drop, s_w, g_tab, ln2kT, dEsum, nacc);
-        __builtin_amdgcn_wave_barrier();
-    }
+    Sums sums = {0, 0u};
+    auto all_rounds = [&](auto mode_tag) {
+        constexpr int MODE = decltype(mode_tag)::value;
+#pragma nounroll
+        for (int m = 0; m < 27; ++m) {
+            const int rx = m % 3, ry = (m / 3) % 3, rz = m / 9;
+            const uint64_t valid =
+                __builtin_amdgcn_ballot_w64((3 * ix < wx - rx) & (3 * iy < wy - ry) & (3 * iz < wz - rz));
+            uint32_t gx = bx + rx, gy = by + ry, gz = bz + rz;
+            gx = min(gx, gx - (uint32_t)Lx);
+            gy = min(gy, gy - (uint32_t)Ly);
+            gz = min(gz, gz - (uint32_t)Lz);
+            uint64_t cell;
+            if (narrow)
+                cell = __umul24(gz, LxLy) + __umul24(gy, (uint32_t)Lx) + gx;
+            else
+                cell = ((uint64_t)gz * (uint32_t)Ly + gy) * (uint32_t)Lx + gx;
+            // one Philox call per cell: site b accepts with word b
+            uint32_t ra[4] = {(uint32_t)cell, (uint32_t)(cell >> 32), s, (uint32_t)colour};
+            philox4x32_10(ra, k0, k1);
+            const int q0 = 4 * m, pv = q0 < 64 ? part[0] : part[1];   // (readlane takes the lane modulo 64)
+            uint8_t* at = lat + ((rz + 3 * iz) * kPP + (ry + 3 * iy) * kP + (rx + 3 * ix));
+            trial_any<SMAX, MODE, 0>(__builtin_amdgcn_readlane(pv, q0), at, site_addr<0>(0, 0, 0), ra[0], valid, s_w,
+                                     g_tab, ln2kT, sums);
+            __builtin_amdgcn_wave_barrier();
+            trial_any<SMAX, MODE, 1>(__builtin_amdgcn_readlane(pv, q0 + 1), at, site_addr<1>(0, 0, 0), ra[1], valid, s_w,
+                                     g_tab, ln2kT, sums);
+            __builtin_amdgcn_wave_barrier();
+            dEsum += (int64_t)sums.dE;   // (two changes at a time stay inside 32 bits)
+            sums.dE = 0;
+            trial_any<SMAX, MODE, 2>(__builtin_amdgcn_readlane(pv, q0 + 2), at, site_addr<2>(0, 0, 0), ra[2], valid, s_w,
+                                     g_tab, ln2kT, sums);
+            __builtin_amdgcn_wave_barrier();
+            trial_any<SMAX, MODE, 3>(__builtin_amdgcn_readlane(pv, q0 + 3), at, site_addr<3>(0, 0, 0), ra[3], valid, s_w,
+                                     g_tab, ln2kT, sums);
+            __builtin_amdgcn_wave_barrier();
+            dEsum += (int64_t)sums.dE;
+            sums.dE = 0;
+        }
+    };
+    if (dot_codes)
+        all_rounds(std::integral_constant<int, kWtabDot>{});
+    else
+        all_rounds(std::integral_constant<int, kWtabFull>{});
 
     // ---- write back: sublattice b over cells -SUB[b][a] .. w_a - SUB[b][a] ----
     // Rows r = (lane >> 4) + 4 it; the 16 LDS reads of four rows are issued
@@ -456,7 +559,7 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
     }
 
     uint64_t sum = (uint64_t)dEsum;
-    const uint32_t cnt = nacc;   // already the wave's total
+    const uint32_t cnt = sums.nacc;   // already the wave's total
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         const uint32_t lo = __shfl_xor((uint32_t)sum, o, kWave);
