@@ -322,24 +322,8 @@ __device__ __forceinline__ int site_addr(int lx, int ly, int lz)
 
 // Site b of cell l is staged when l_a lies in -1-SUB[b][a] .. w_a+1-SUB[b][a]
 // and written back when l_a lies in -SUB[b][a] .. w_a-SUB[b][a] (the block's
-// own cells and the partners its trials can reach).
-__device__ __forceinline__ bool in_halo(int b, int lx, int ly, int lz, int wx, int wy, int wz)
-{
-    const int sx = SUB[b][0], sy = SUB[b][1], sz = SUB[b][2];
-    return lx >= -1 - sx && lx <= wx + 1 - sx && ly >= -1 - sy && ly <= wy + 1 - sy && lz >= -1 - sz &&
-           lz <= wz + 1 - sz;
-}
-
-__device__ __forceinline__ bool in_write_box(int b, int lx, int ly, int lz, int wx, int wy, int wz)
-{
-    const int sx = SUB[b][0], sy = SUB[b][1], sz = SUB[b][2];
-    return lx >= -sx && lx <= wx - sx && ly >= -sy && ly <= wy - sy && lz >= -sz && lz <= wz - sz;
-}
-
-__device__ __forceinline__ int lds_index(int b, int lx, int ly, int lz)
-{
-    return b * kArr + (lz + 1 + SUB[b][2]) * kPP + (ly + 1 + SUB[b][1]) * kP + (lx + 1 + SUB[b][0]);
-}
+// own cells and the partners its trials can reach); its byte in the image is
+// b*kArr + (lz+1+SUB[b][2])*kPP + (ly+1+SUB[b][1])*kP + (lx+1+SUB[b][0]).
 
 }  // namespace fcc
 
@@ -424,31 +408,67 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
 
     const bool dot_codes = D.drop_last == kWtabDot;   // LDS codes for the byte-dot weight rows
     // ---- stage block + halo: one cell (4 sublattice bytes, one dword) per lane ----
-    // Rows r = (lane >> 4) + 4 it; the loads of 16 rows are issued together
-    // (lanes and rows outside the halo load a clamped in-range cell).
+    // Lane row lr = lane >> 4 takes the cells lx = (lane & 15) - 2 of rows
+    // ly = lr - 2 + 4 j (j = 0..3) of each plane lz = -2 .. wz + 1.  The lane's
+    // four row addresses are set up once; a plane adds its offset, which is
+    // wave-uniform.  The loads of kPlanesF planes are issued together.  Lanes
+    // and rows past the halo (w < 12) load an in-range cell and write it to
+    // image positions past w + 1, which no trial with a site and no write-back
+    // reads; only positions outside the 15^3 arrays (-2 or, where the
+    // sublattice's origin is half a cell lower, 13) are not written.  The
+    // writes of one sublattice share their lane mask: -2 and 13 of x for all,
+    // of y in the first or the last of the four rows.
+    const int64_t plane_bytes = 4 * (int64_t)Lx * Ly;
+    constexpr int kPlanesF = 4;
     if (active) {
-        const int lx = (lane & 15) - 2;
-        const bool okx = lx <= wx + 1;
-        const int gx = wrap_add(gx0 + (okx ? lx : -2), Lx);
-        for (int it0 = 0; it0 < 64; it0 += 16) {
-            uint32_t v16[16];
+        // codes of species 0..7 as a byte table (species >= KMAXF never occur)
+        uint32_t code_lo = 0u, code_hi = 0u;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int it = it0 + u;
-                const int ly = min((lane >> 4) + 4 * (it & 3) - 2, wy + 1), lz = min((it >> 2) - 2, wz + 1);
-                const int gy = wrap_add(gy0 + ly, Ly), gz = wrap_add(gz0 + lz, Lz);
-                v16[u] = gload<uint32_t>(g + 4 * (((size_t)gz * Ly + gy) * Lx + gx));
+        for (uint32_t v = 0; v < KMAXF; ++v) {
+            const uint32_t c = (dot_codes ? encode4_dot<KMAXF>(v) : (v << 5) + (v << 2) + (v << 1)) & 0xffu;
+            if (v < 4) code_lo |= c << (8 * v);
+            else code_hi |= c << (8 * (v - 4));
+        }
+        asm volatile("" : "+v"(code_lo));   // (v_perm_b32 reads at most one scalar operand)
+        const int lr = lane >> 4, lx = (lane & 15) - 2;
+        const int gx = wrap_add(gx0 + (lx <= wx + 1 ? lx : -2), Lx);
+        const uint8_t* row[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int gy = wrap_add(gy0 + min(lr + 4 * j - 2, wy + 1), Ly);
+            row[j] = g + 4 * ((size_t)gy * Lx + gx);
+        }
+        // cell (-1, -1, -1) of sublattice 0 is byte 0 of the image
+        uint8_t* at = lat + (lr - 1) * kP + (lx + 1);
+#pragma nounroll
+        for (int lz0 = -2; lz0 <= wz + 1; lz0 += kPlanesF) {
+            uint32_t v[kPlanesF][4];
+#pragma unroll
+            for (int k = 0; k < kPlanesF; ++k) {
+                const int64_t plane = (int64_t)wrap_add(gz0 + min(lz0 + k, wz + 1), Lz) * plane_bytes;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[k][j] = gload<uint32_t>(row[j] + plane);
             }
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int it = it0 + u;
-                const int ly = (lane >> 4) + 4 * (it & 3) - 2, lz = (it >> 2) - 2;
-                if (!okx || ly > wy + 1 || lz > wz + 1) continue;
-                uint32_t v = v16[u];
-                v = dot_codes ? encode4_dot<KMAXF>(v) : (v << 5) + (v << 2) + (v << 1);   // else (6 + 32) * species
+            for (int k = 0; k < kPlanesF; ++k)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (in_halo(b, lx, ly, lz, wx, wy, wz)) lat[lds_index(b, lx, ly, lz)] = (uint8_t)(v >> (8 * b));
+                for (int j = 0; j < 4; ++j) v[k][j] = __builtin_amdgcn_perm(code_hi, code_lo, v[k][j]);
+            uint8_t* at0 = at + (lz0 + 1) * kPP;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int sx = SUB[b][0], sy = SUB[b][1], sz = SUB[b][2];
+                auto put = [&](int j) {
+#pragma unroll
+                    for (int k = 0; k < kPlanesF; ++k)
+                        if (sz ? lz0 + k <= 12 : lz0 + k >= -1)   // (wave-uniform)
+                            at0[b * kArr + (k + sz) * kPP + (4 * j + sy) * kP + sx] = (uint8_t)(v[k][j] >> (8 * b));
+                };
+                if (sx ? lx <= 12 : lx >= -1) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j != (sy ? 3 : 0)) put(j);
+                    if (sy ? lr <= 2 : lr >= 1) put(sy ? 3 : 0);   // (ly <= 12, ly >= -1)
+                }
             }
         }
     }
@@ -514,45 +534,52 @@ void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem*
         all_rounds(std::integral_constant<int, kWtabFull>{});
 
     // ---- write back: sublattice b over cells -SUB[b][a] .. w_a - SUB[b][a] ----
-    // Rows r = (lane >> 4) + 4 it; the 16 LDS reads of four rows are issued
-    // together (rows and cells outside the boxes read clamped in-image bytes
-    // and store nothing).
+    // Lane row lr takes the cells lx = (lane & 15) - 1 of rows ly = lr - 1 + 4 j
+    // of each plane lz = -1 .. wz; the 16 LDS reads of a plane are issued
+    // together (lanes and rows outside the boxes read clamped in-image bytes
+    // and store nothing).  Cells with all four sublattices in their boxes,
+    // 0 .. w_a - 1 on each axis, are stored as a word; of the cells around
+    // them each sublattice's own byte.
     {
-        const int lx = (lane & 15) - 1;
-        const bool okx = lx <= wx;
-        const int lxc = okx ? lx : 0;
+        const int lr = lane >> 4, lx = (lane & 15) - 1;
         const int gx = wrap_add(gx0 + lx, Lx);
-        const int nit = 4 * (wz + 2);               // rows with lz <= wz
-        for (int it0 = 0; it0 < nit; it0 += 4) {
+        const bool inner_x = lx >= 0 && lx < wx;
+        uint8_t* row[4];
+        int src[4];
+        bool inner[4], box[4][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int ly = lr + 4 * j - 1;
+            row[j] = g + 4 * ((size_t)wrap_add(gy0 + min(ly, wy), Ly) * Lx + gx);
+            src[j] = (min(ly, wy) + 1) * kP + (min(lx, wx) + 1);
+            inner[j] = inner_x && ly >= 0 && ly < wy;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int sx = SUB[b][0], sy = SUB[b][1];
+                box[j][b] = lx >= -sx && lx <= wx - sx && ly >= -sy && ly <= wy - sy;
+            }
+        }
+#pragma nounroll
+        for (int lz = -1; lz <= wz; ++lz) {
+            const int64_t plane = (int64_t)wrap_add(gz0 + lz, Lz) * plane_bytes;
+            const bool inner_z = lz >= 0 && lz < wz;   // wave-uniform
+            const uint8_t* at = lat + (lz + 1) * kPP;
             uint32_t c[4][4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int it = it0 + u;
-                const int lyc = min((lane >> 4) + 4 * (it & 3) - 1, wy), lzc = min((it >> 2) - 1, wz);
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) c[u][b] = lat[lds_index(b, lxc, lyc, lzc)];
-            }
+                for (int b = 0; b < 4; ++b)
+                    c[j][b] = at[src[j] + b * kArr + SUB[b][2] * kPP + SUB[b][1] * kP + SUB[b][0]];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int it = it0 + u;
-                const int ly = (lane >> 4) + 4 * (it & 3) - 1, lz = (it >> 2) - 1;
-                if (!okx || ly > wy || lz > wz) continue;
-                bool v[4];
-                uint32_t e = 0u;
+            for (int j = 0; j < 4; ++j) {
+                uint8_t* q = row[j] + plane;
+                if (inner_z && inner[j])
+                    gstore<uint32_t>(q, decode(c[j][0]) | decode(c[j][1]) << 8 | decode(c[j][2]) << 16 |
+                                            decode(c[j][3]) << 24);
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    v[b] = in_write_box(b, lx, ly, lz, wx, wy, wz);
-                    e |= decode(c[u][b]) << (8 * b);
-                }
-                if (!(v[0] || v[1] || v[2] || v[3])) continue;
-                const int gy = wrap_add(gy0 + ly, Ly), gz = wrap_add(gz0 + lz, Lz);
-                uint8_t* q = g + 4 * (((size_t)gz * Ly + gy) * Lx + gx);
-                if (v[0] && v[1] && v[2] && v[3]) {
-                    gstore<uint32_t>(q, e);
-                } else {
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        if (v[b]) gstore<uint8_t>(q + b, (uint8_t)(e >> (8 * b)));
+                    const bool box_z = SUB[b][2] ? lz < wz : lz >= 0;
+                    if (box_z && box[j][b] && !(inner_z && inner[j])) gstore<uint8_t>(q + b, (uint8_t)decode(c[j][b]));
                 }
             }
         }
