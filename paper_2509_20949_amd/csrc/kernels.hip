@@ -650,18 +650,23 @@ static hipError_t launch_bcc(const DevLattice* d_lat, const WorkItem* d_items, i
 }
 
 // Colour launches of at most this many blocks give a block four waves
-// (kernels_split.hip): the workgroups of 768 blocks are resident at once
-// (42 KB of LDS each, three to a CU).  us per launch, K = 5, S = 3, one wave
-// per block against four: 27 blocks 42.0 and 19.5, 216 42.5 and 20.0, 512
-// 43.1 and 27.2, 729 44.4 and 35.1, 1,000 (a second generation) 44.6 and
-// 44.6, 1,728 51.2 and 68.4; K = 8, S = 3: 729 54.6 and 49.0, 1,000 54.8 and
-// 64.9; K = 2, S = 1: 729 35.0 and 24.9, 1,728 40.9 and 43.8.
-constexpr int kSplitBlocks = 768;
+// (kernels_split.hip).  Their time rises by a step with every 256 blocks (a
+// workgroup to each CU) until three are resident (42 KB of LDS each), while
+// one wave per block takes the same time up to 1,024 blocks (a workgroup of
+// four blocks to each CU): the lines cross between 512 and 513 blocks, at
+// K = 2, S = 1 between 768 and 769.  us per launch, one wave per block
+// against four: K = 5, S = 3: 64 blocks 31.8 and 19.5, 256 32.4 and 20.0, 512
+// 33.2 and 26.5, 576 33.4 and 33.8, 729 33.8 and 33.9, 800 33.9 and 43.7;
+// K = 8, S = 3: 512 45.0 and 37.0, 576 45.0 and 49.0; K = 4, S = 2: 512 28.2
+// and 22.6, 576 28.4 and 27.6; K = 2, S = 1: 729 24.9 and 23.8, 800 25.1 and
+// 28.1.
+constexpr int kSplitBlocks = 512;
 // FCC (37 KB of LDS, four workgroups to a CU; kernels_fcc_split.hip), us per
-// launch at K = 5, S = 3, one wave per block against four: 1 block 113 and
-// 41, 216 116 and 43, 512 117 and 59, 1,000 135 and 97, 1,331 (a second
-// generation) 136 and 136, 1,728 138 and 156; K = 3, S = 1: 1,000 94 and 59.
-constexpr int kSplitBlocksFcc = 1024;
+// launch at K = 5, S = 3, one wave per block against four: 64 blocks 79.6 and
+// 43.0, 256 79.6 and 44.0, 512 80.5 and 58.8, 576 93.8 and 77.7, 729 94.2 and
+// 78.7, 800 94.7 and 96.8, 1,000 95.3 and 97.4, 1,100 100.4 and 117.9.  (K = 3,
+// S = 1: 1,000 66.7 and 58.1, 1,100 66.9 and 72.3.)
+constexpr int kSplitBlocksFcc = 768;
 
 hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int n_blocks,
                               int t, int colour, int kmax, int smax, hipStream_t stream, bool slab, int wpg)

@@ -12,13 +12,13 @@ from paper_2509_20949_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-# blocks per colour 6 * 12 * 10 = 720 and 6 * 12 * 11 = 792 around the rule's
-# 768; widths 12 (whole rounds), 2 (the narrowest) and 5..6 (partial lanes)
-FEW = dict(L=(144, 48, 113), block=(12, 2, 6), blocks=720)
-MANY = dict(L=(144, 48, 125), block=(12, 2, 6), blocks=792)
-# FCC: 6 * 12 * 14 = 1008 and 6 * 12 * 15 = 1080 around 1024
-FCC_FEW = dict(L=(144, 48, 161), block=(12, 2, 6), blocks=1008)
-FCC_MANY = dict(L=(144, 48, 173), block=(12, 2, 6), blocks=1080)
+# blocks per colour 6 * 12 * 7 = 504 and 6 * 12 * 8 = 576 around the rule's
+# 512; widths 12 (whole rounds), 2 (the narrowest) and 5..6 (partial lanes)
+FEW = dict(L=(144, 48, 77), block=(12, 2, 6), blocks=504)
+MANY = dict(L=(144, 48, 89), block=(12, 2, 6), blocks=576)
+# FCC: 6 * 12 * 10 = 720 and 6 * 12 * 11 = 792 around 768
+FCC_FEW = dict(L=(144, 48, 113), block=(12, 2, 6), blocks=720)
+FCC_MANY = dict(L=(144, 48, 125), block=(12, 2, 6), blocks=792)
 
 
 def note(msg):
@@ -92,7 +92,7 @@ def test_fcc_full_rows_around_the_rule(smcx, orc, shape):
     run(smcx, orc, shape, epi, 5000.0, 45, n_sweeps=1, lattice=1)
 
 
-@pytest.mark.parametrize("L,B,blocks", [((48, 48, 120), (2, 2, 12), 720), ((48, 48, 144), (2, 2, 12), 864)])
+@pytest.mark.parametrize("L,B,blocks", [((48, 48, 72), (2, 2, 12), 432), ((48, 48, 96), (2, 2, 12), 576)])
 def test_slab_kernels_around_the_rule(smcx, orc, L, B, blocks):
     import torch
     job = W.lattice_job(L, 5, 3, 30.0, np.full(2, 950.0), stream=150, name="slab")
