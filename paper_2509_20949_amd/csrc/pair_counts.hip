@@ -401,55 +401,78 @@ struct Planes {
 };
 
 // Species planes of one z plane, the plane addressed by a buffer resource:
-// row b (bit b) is row y = ystart + b (wrapped) at byte offset NSUB y Lx +
-// xo, stepped row by row on the scalar unit; one row per instruction, 8 rows
-// ahead of their use.
+// row b (bit b) is row y = (y0 - 1) + b (wrapped) at byte offset NSUB y Lx +
+// xo, one row per instruction.  Rows come in steps of 16, eight from each of
+// two runs 16 rows apart (ystart[q]: first row of run q), each run stepped row
+// by row on the scalar unit; a step's loads are issued a step ahead.
+// A cell's bytes hold three bits each: row b + 4 goes into the free nibble
+// bits of row b's word and (two sublattices, 16 bits a cell) the rows 16 on
+// into its upper half, so that one shift and one v_and_or take the same bit of
+// four (FCC: two) rows to their places.  512^3 sites x 2, K = 5, S = 3: 12
+// instructions a row and 253 us a kernel with a v_bfe and a v_lshl_or per bit.
 template <int NSUB, int KM1>
-__device__ __forceinline__ void build_planes(__amdgpu_buffer_rsrc_t rs, int ystart, int Ly, uint32_t row_bytes,
-                                             uint32_t xo, Planes<NSUB, KM1>& P)
+__device__ __forceinline__ void build_planes(__amdgpu_buffer_rsrc_t rs, const int (&ystart)[4], int Ly,
+                                             uint32_t row_bytes, uint32_t xo, Planes<NSUB, KM1>& P)
 {
-    int y = ystart;
-    uint32_t so = (uint32_t)ystart * row_bytes;
-    auto load = [&](int) -> uint32_t {
-        const uint32_t v = NSUB == 4 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)xo, (int)so, 0)
-                                     : (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)xo, (int)so, 0);
-        if (++y == Ly) {
-            y = 0;
-            so = 0;
-        } else {
-            so += row_bytes;
-        }
-        return v;
-    };
+    constexpr int R = 8;   // rows of a run per step
     uint32_t S[NSUB][3][2] = {};   // [sublattice][species bit][half]
-    constexpr int R = 8;           // rows per group
-    uint32_t c[R], cn[R];
+    uint32_t c[2][R], cn[2][R];
+    int y[2];
+    uint32_t so[2];
+    // rows 8 t .. 8 t + 7 of runs 2 h and 2 h + 1 (step = 2 h + t)
+    auto load = [&](uint32_t (&to)[2][R], int step) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) c[r] = load(r);
+        for (int q = 0; q < 2; ++q) {
+            if ((step & 1) == 0) {
+                y[q] = ystart[step + q];
+                so[q] = (uint32_t)y[q] * row_bytes;
+            }
 #pragma unroll
-    for (int grp = 0; grp < 64 / R; ++grp) {
-        if (grp < 64 / R - 1) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) cn[r] = load(R * (grp + 1) + r);
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int b = R * grp + r;
-#pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    // one v_bfe and one v_lshl_or per bit, in a chain per
-                    // word (not an OR tree, which holds every term at once)
-                    S[sub][i][b >> 5] |= ((c[r] >> (8 * sub + i)) & 1u) << (b & 31);
-                    keep(S[sub][i][b >> 5]);
+            for (int r = 0; r < R; ++r) {
+                to[q][r] = NSUB == 4 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)xo, (int)so[q], 0)
+                                     : (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)xo, (int)so[q], 0);
+                if (++y[q] == Ly) {
+                    y[q] = 0;
+                    so[q] = 0;
+                } else {
+                    so[q] += row_bytes;
                 }
+            }
         }
-        if (grp < 64 / R - 1) {
+    };
+    load(c, 0);
 #pragma unroll
-            for (int r = 0; r < R; ++r) c[r] = cn[r];
+    for (int step = 0; step < 4; ++step) {
+        if (step < 3) load(cn, step + 1);
+        const int h = step >> 1, t = step & 1;
+#pragma unroll
+        for (int r = 0; r < R / 2; ++r) {
+            const uint32_t lo = c[0][r] | c[0][r + 4] << 4, hi = c[1][r] | c[1][r + 4] << 4;
+            // bits at row `row` (and 4, 16, 20 on) of the word
+            auto take = [&](uint32_t w, uint32_t mask, int row) {
+#pragma unroll
+                for (int sub = 0; sub < NSUB; ++sub)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const int n = row - (8 * sub + i);
+                        S[sub][i][h] |= (n >= 0 ? w << n : w >> -n) & (mask << row);
+                        keep(S[sub][i][h]);   // a chain per word (an OR tree holds every term at once)
+                    }
+            };
+            if constexpr (NSUB == 2) {
+                take(lo | hi << 16, 0x00110011u, 8 * t + r);
+            } else {
+                take(lo, 0x11u, 8 * t + r);
+                take(hi, 0x11u, 16 + 8 * t + r);
+            }
         }
-        // keep the scheduler from hoisting later groups' loads (each would
+        if (step < 3) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int r = 0; r < R; ++r) c[q][r] = cn[q][r];
+        }
+        // keep the scheduler from hoisting later steps' loads (each would
         // hold a register until its row is used)
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -505,7 +528,7 @@ void pair_counts_planes_kernel(const uint8_t* __restrict__ g, int Lx, int Ly, in
     const int zb = zi * zc, ze = min(Lz, zb + zc);
     const int wx = min(pc::kTile, Lx - x0), wy = min(pc::kTile, Ly - y0);
     const int xl = (x0 - 1 + lane + Lx) % Lx;
-    const int ystart = (y0 - 1 + Ly) % Ly;
+    const int ystart[4] = {(y0 - 1 + Ly) % Ly, (y0 + 15) % Ly, (y0 + 31) % Ly, (y0 + 47) % Ly};
     const uint32_t row_bytes = (uint32_t)NSUB * (uint32_t)Lx;
     const uint32_t xo = (uint32_t)NSUB * (uint32_t)xl;
     // the tile's own sites: lanes 1..wx, bits 1..wy
