@@ -543,6 +543,11 @@ void pair_counts_planes_kernel(const uint8_t* __restrict__ g, int Lx, int Ly, in
 
     Planes<NSUB, KM1> W0, W1;   // planes z and z + 1
     build_planes<NSUB, KM1>(zrsrc(zb), ystart, Ly, row_bytes, xo, W0);
+    // Bonds of shell m with both ends of species a or b (a < b), or both of
+    // species a ([a][a]).  The counts wanted are symmetric,
+    // B[a][b] + B[b][a] = U[a][b] - U[a][a] - U[b][b], so K (K - 1) / 2 unions
+    // replace the (K - 1)^2 ordered pairs: 10 against 16 counts a bond and
+    // half at K = 5 for 6 ORs.
     uint32_t acc[SMAX][KA][KA] = {};
     uint32_t nsp[KA] = {};
 #pragma nounroll
@@ -550,13 +555,15 @@ void pair_counts_planes_kernel(const uint8_t* __restrict__ g, int Lx, int Ly, in
         build_planes<NSUB, KM1>(zrsrc(z + 1), ystart, Ly, row_bytes, xo, W1);
         auto centre = [&](auto sc) {
             constexpr int s = decltype(sc)::value;
-            uint32_t C[KA][2];
+            uint32_t C[KA][KA][2];   // [a][b], a <= b: the centre sites of species a or b
 #pragma unroll
-            for (int a = 0; a < KM1; ++a) {
+            for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    C[a][h] = W0.p[s][a][h] & ymask[h];
-                    nsp[a] += (uint32_t)__popc(C[a][h]);
+                for (int b = 0; b < KM1; ++b) {
+                    C[b][b][h] = W0.p[s][b][h] & ymask[h];
+                    nsp[b] += (uint32_t)__popc(C[b][b][h]);
+#pragma unroll
+                    for (int a = 0; a < b; ++a) C[a][b][h] = C[a][a][h] | C[b][b][h];
                 }
             }
             auto shell = [&](auto mc) {
@@ -566,17 +573,24 @@ void pair_counts_planes_kernel(const uint8_t* __restrict__ g, int Lx, int Ly, in
                         constexpr int k = decltype(kc)::value;
                         constexpr pc::ZBond d = T::bonds.b[s][m][k];
                         const Planes<NSUB, KM1>& N = d.dz ? W1 : W0;
+                        uint32_t lo[KA], hi[KA];
 #pragma unroll
                         for (int b = 0; b < KM1; ++b) {
-                            uint32_t lo = N.p[d.sub][b][0], hi = N.p[d.sub][b][1];
-                            yshift<d.dy>(lo, hi);
-                            lo = xshift<d.dx>(lo);
-                            hi = xshift<d.dx>(hi);
-#pragma unroll
-                            for (int a = 0; a < KM1; ++a)
-                                acc[m][a][b] += (uint32_t)__popc(C[a][0] & lo) + (uint32_t)__popc(C[a][1] & hi);
+                            lo[b] = N.p[d.sub][b][0];
+                            hi[b] = N.p[d.sub][b][1];
+                            yshift<d.dy>(lo[b], hi[b]);
+                            lo[b] = xshift<d.dx>(lo[b]);
+                            hi[b] = xshift<d.dx>(hi[b]);
                         }
-                        // one bond at a time (its 2 (K - 1)^2 ANDs and bit
+#pragma unroll
+                        for (int b = 0; b < KM1; ++b) {
+                            acc[m][b][b] += (uint32_t)__popc(C[b][b][0] & lo[b]) + (uint32_t)__popc(C[b][b][1] & hi[b]);
+#pragma unroll
+                            for (int a = 0; a < b; ++a)
+                                acc[m][a][b] += (uint32_t)__popc(C[a][b][0] & (lo[a] | lo[b])) +
+                                                (uint32_t)__popc(C[a][b][1] & (hi[a] | hi[b]));
+                        }
+                        // one bond at a time (its K (K - 1) ANDs and bit
                         // counts are independent work enough): shifted planes
                         // of later bonds are not computed ahead
                         __builtin_amdgcn_sched_barrier(0);
@@ -614,11 +628,11 @@ void pair_counts_planes_kernel(const uint8_t* __restrict__ g, int Lx, int Ly, in
     };
 #pragma unroll
     for (int m = 0; m < SMAX; ++m) {
-        int64_t B[KA][KA];
+        int64_t U[KA][KA];
 #pragma unroll
         for (int a = 0; a < KM1; ++a)
 #pragma unroll
-            for (int b = 0; b < KM1; ++b) B[a][b] = (int64_t)wsum(acc[m][a][b]);
+            for (int b = a; b < KM1; ++b) U[a][b] = (int64_t)wsum(acc[m][a][b]);
         if (lane == 0) {
             const int64_t Z = pc::kZm[LAT][m];
             int64_t lastrow = Z * nlast;
@@ -627,7 +641,7 @@ void pair_counts_planes_kernel(const uint8_t* __restrict__ g, int Lx, int Ly, in
                 int64_t row = 0;
 #pragma unroll
                 for (int b = 0; b < KM1; ++b) {
-                    const int64_t v = B[a][b] + B[b][a];
+                    const int64_t v = a == b ? 2 * U[a][a] : U[a < b ? a : b][a < b ? b : a] - U[a][a] - U[b][b];
                     row += v;
                     if (b >= a) {
                         add(m, a, b, v);
