@@ -101,15 +101,13 @@ __device__ __forceinline__ uint32_t count_swap(uint32_t start, uint32_t a, uint3
 
 // LDS form of the pair-weight table: entry f of row (a, b) (f = s*KMAX + p
 // for a weight, SMAX*KMAX for the constant) sits in plane f at position
-// a*KMAX + b, planes wplane(KMAX) dwords apart.  The lanes of a wave read one
+// a*KMAX + b, planes kPlane dwords apart.  The lanes of a wave read one
 // plane per instruction, each at its own row: distinct rows fall in distinct
 // 4-byte banks, equal rows broadcast (a row-per-lane layout made most lanes
 // collide, its rows all starting on the same few banks).
-constexpr int wplane(int kmax) { return ((kmax * kmax + 31) / 32) * 32; }
 constexpr int wplanes(int kmax, int smax) { return wrow_entries(kmax, smax); }
 
-// Weight planes of the BCC kernels and of the trials four lanes share: row (a, b) at position a*KMAX + b of a
-// 64-entry plane, so that the position of any two 3-bit codes (a lane
+// Planes of 64 entries, so that the position of any two 3-bit codes (a lane
 // without a site may decode a stale halo byte) stays inside its plane.  The
 // KMAX^2 rows of real species then lie in distinct LDS banks (positions
 // 8a + b, one multiply fewer, put species 4 and 0 of K = 5 on the same
@@ -117,17 +115,6 @@ constexpr int wplanes(int kmax, int smax) { return wrow_entries(kmax, smax); }
 constexpr int kPlane = 64;
 static_assert(7 * kMaxK + 7 < kPlane, "weight plane too narrow");
 
-// Fill the LDS planes (PS dwords apart, PS >= KMAX*KMAX) from the
-// row-major table of wrow(KMAX, SMAX) ints per row.
-template <int KMAX, int SMAX, int PS = wplane(KMAX)>
-__device__ __forceinline__ void load_wplanes(int32_t* s_w, const int32_t* wtab)
-{
-    constexpr int WR = wrow(KMAX, SMAX);
-    for (int k = threadIdx.x; k < wplanes(KMAX, SMAX) * PS; k += blockDim.x) {
-        const int f = k / PS, row = k - f * PS;
-        s_w[k] = row < KMAX * KMAX ? wtab[row * WR + f] : 0;
-    }
-}
 
 // Byte-dot codes (weight rows in kWtabDot form, KMAX <= 5): species
 // v < KMAX-1 is stored as 40 v, i.e. counted by a shift of 8 v into byte v
@@ -231,9 +218,9 @@ __device__ __forceinline__ void accept_bounds(uint32_t u, float c, int& lo, int&
 
 // The Metropolis test of Eq. (3) for the draw u as two edges on float(dE):
 // dE <= lo is accepted and dE > hi rejected without the tables.  From e as in
-// accept_edges (device_common.h): hi = e + 8; lo = e - 8, but at least 0, so
-// that dE <= 0 passes, and at most the lower edge of u = 1, which u = 0 (e =
-// +inf, its upper edge too) passes as well.
+// accept_edges: hi = e + 8; lo = e - 8, but at least 0, so that dE <= 0
+// passes, and at most the lower edge of u = 1, which u = 0 (e = +inf, its
+// upper edge too) passes as well.
 struct Edges {
     float lo, hi;
 };

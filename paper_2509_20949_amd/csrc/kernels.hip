@@ -85,10 +85,13 @@ __device__ __forceinline__ uint32_t weigh(const uint32_t (&hi)[kMaxS], const uin
 //          (x, y, z + 1) before the body trial; one cell on in x after it
 // A trial finds its site, its partner, its first shell and 10 of its 18
 // second and third neighbours here, and loads the cells that enter the window.
-// Each trial puts its own changes into the window; no other lane changes a
-// cell of it within the x row: in units of a/2, trials of one round are 6
-// apart and change cells within 1, the window reaches 4 ahead of the row's
-// first site and 3 behind, on the axes and sides where it holds cells.
+// Each trial puts its own changes into the window.  No other lane changes a
+// cell while the window holds it: in units of a/2, the lanes' sites of a round
+// are 6 apart on some axis, move along the row together, and a trial changes
+// cells within 1 of its site, so only cells 5 or more from a lane's site are
+// ever changed by another; every cell is within 2 of a site that reads it, and
+// is taken in at most two trials (1 each along x) before and dropped at most
+// two after.
 //   pc, pb the packed counts (with the fields' bias) of the four cells of a
 //          plane around the row's axis -- (x, y +- 1, z), (x, y, z +- 1) --
 //          for the planes x - 1 and x of the corner (body) sublattice: four
@@ -432,6 +435,13 @@ __device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, u
 }
 
 // ---------------------------------------------------------------------------
+// What bounds it (512^3, K = 5, S = 3, a colour launch of N/8 trials): issue of
+// vector and LDS instructions together.  The launch took 164 us when each
+// trial loaded 32 cells; with the row window (fewer loads, plane sums in place
+// of single counts), scalar decision masks and the set-up reads overlapped it
+// takes 133 us: 118 VALU, 36 LDS and 54 scalar instructions per wave-round, no
+// bank conflicts.  Staging, set-up and write-back are about a third of a
+// wave's time in the first generation of a launch.
 // SLAB: the lattice is a z-slab (DevLattice::slab) -- its own instance, so
 // the periodic kernel carries none of the slab's addressing.  WPG: blocks
 // (waves) per workgroup, kWavesPerGroup (5 workgroups, 20 waves per CU,

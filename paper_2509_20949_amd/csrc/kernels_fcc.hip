@@ -330,6 +330,12 @@ __device__ __forceinline__ int site_addr(int lx, int ly, int lz)
 // WPG waves (blocks) per workgroup: 2 (five workgroups per CU, LDS-bound), or
 // kWavesPerGroupFccWide for a single lattice whose colour then fits the chip
 // in fewer generations (one workgroup of 11 block images fills a CU's LDS).
+// What bounds it (336 x 315 x 315 cells, S = 3, 11 waves on a CU, so three on
+// most SIMDs): vector issue of those SIMDs, about 0.7 of the time, and the
+// LDS, 0.63 of it; 150 VALU, 68 LDS and 49 scalar instructions per wave-round.
+// 166 us a launch before the site and partner were loaded first (150), the
+// partner's arms stood behind flat tests (143) and staging and write-back were
+// set up once per lane (136).
 template <int SMAX, int WPG>
 __global__ __launch_bounds__(kWave * WPG)
 void sweep_phase_fcc_kernel(const DevLattice* __restrict__ lats, const WorkItem* __restrict__ items, int n_groups,

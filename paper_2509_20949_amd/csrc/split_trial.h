@@ -76,9 +76,8 @@ template <int N> __device__ __forceinline__ uint32_t count_all(uint32_t bias, co
 // The acceptance edge of a draw (Eq. (3)): a change dE with float(dE) <= lo
 // is accepted without the threshold tables, one with float(dE) > lo + 16 is
 // rejected, in between the table decides (accept_edges, device_common.h: lo
-// is its lower edge, but never below 0, so that dE <= 0 passes; with the
-// upper edge taken as lo + 16 the band only grows or shifts by the two
-// roundings, 1 micro-eV of the 4.7 in hand).  Every edge of a draw u > 0 lies
+// is its lower edge, but never below 0, so that dE <= 0 passes; lo + 16 is
+// its upper edge, or above it where lo was raised to 0).  Every edge of a draw u > 0 lies
 // below 2^24 - 16.  A trial without a site gets -inf (always rejected), u = 0
 // NaN (neither test passes: the table decides).
 __device__ __forceinline__ float accept_edge(uint32_t u, float ln2kT, bool valid)
