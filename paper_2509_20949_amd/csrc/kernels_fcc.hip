@@ -331,8 +331,9 @@ __device__ __forceinline__ int site_addr(int lx, int ly, int lz)
 // kWavesPerGroupFccWide for a single lattice whose colour then fits the chip
 // in fewer generations (one workgroup of 11 block images fills a CU's LDS).
 // What bounds it (336 x 315 x 315 cells, S = 3, 11 waves on a CU, so three on
-// most SIMDs): vector issue of those SIMDs, about 0.7 of the time, and the
-// LDS, 0.63 of it; 150 VALU, 68 LDS and 49 scalar instructions per wave-round.
+// most SIMDs): latency with three waves to hide it, vector issue (0.59 of those
+// SIMDs' cycles) and the LDS (busy 0.52); 139 VALU, 63 LDS and 45 scalar
+// instructions per wave-round.
 // 166 us a launch before the site and partner were loaded first (150), the
 // partner's arms stood behind flat tests (143) and staging and write-back were
 // set up once per lane (136).
