@@ -479,7 +479,7 @@ __device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, u
 // vector and LDS instructions together.  The launch took 164 us when each
 // trial loaded 32 cells; with the row window (fewer loads, plane sums in place
 // of single counts), scalar decision masks and the set-up reads overlapped it
-// takes 133 us: 113 VALU, 36 LDS and 47 scalar instructions per wave-round, no
+// takes 132 us: 108 VALU, 36 LDS and 44 scalar instructions per wave-round, no
 // bank conflicts.  Staging, set-up and write-back are about a third of a
 // wave's time in the first generation of a launch.
 // SLAB: the lattice is a z-slab (DevLattice::slab) -- its own instance, so
