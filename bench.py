@@ -6,7 +6,7 @@ shells 1-3 (int32 micro-eV, entries ~ N(0, 30 meV)), T = 800 K, synthetic
 seeded inputs shaped like the paper's quinary alloy workload.  The lattice
 is resident in HBM before the timed region starts.
 
-Prints one JSON line (the driver's contract) with, besides throughput:
+Prints one JSON line (the benchmark's contract) with, besides throughput:
   roofline      the sweep kernel's algorithmic HBM bytes (2 per trial)
                 against 8 TB/s, timed with HIP events on the stream it runs
                 on, with the copy-calibrated measured traffic;
