@@ -246,3 +246,24 @@ def test_server_above_and_below_the_rule(smcx, orc, kind, K, S, rows):
             assert E == int(ref.E[0]) and accepted == int(ref.accepted[0])
     finally:
         smcx.smcx_server_destroy(srv)
+
+
+@pytest.mark.parametrize("lattice,K", [(0, 2), (0, 3), (0, 4), (0, 5), (1, 2), (1, 3), (1, 4), (1, 5)])
+def test_pair_counts_of_species_unions(smcx, orc, lattice, K):
+    """Lattices of 2^22 cells and more count unions of two species: random
+    sites, without the first or the last species, and all of one species."""
+    L = (130, 131, 247)
+    assert L[0] * L[1] * L[2] >= 1 << 22
+    N = W.n_sites(L, lattice)
+    rng = np.random.default_rng(40 + K)
+    sites = rng.integers(0, K, N, dtype=np.uint8)
+    for S in (1, 2, 3):
+        epi = folded_epi(K, S)
+        for what, sigma in (("random", sites), ("no first", np.maximum(sites, 1)), ("no last", np.minimum(sites, K - 2)),
+                            ("one", np.full(N, K // 2, np.uint8))):
+            note(f"pair counts lattice={lattice} K={K} S={S} {what}")
+            lat = smcx.Lattice(L, epi, sigma, 1, 900.0, lattice=lattice)
+            try:
+                assert np.array_equal(lat.sro()[1], orc.sro(L, S, K, sigma, lattice)[1])
+            finally:
+                lat.close()
