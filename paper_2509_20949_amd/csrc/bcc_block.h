@@ -47,7 +47,7 @@ struct BccBlock {
     int Lx, Ly, Lz;
     int wx, wy, wz;          // block width per axis
     int gx0, gy0, gz0;       // global coordinate of local cell 0
-    uint32_t s, LxLy;
+    uint32_t LxLy;
     uint64_t plane_bytes;    // a plane of the lattice (or the slab buffer)
     uint64_t buf_bytes;
     bool plane32;            // a row's byte offsets fit 31 bits
@@ -89,7 +89,7 @@ __device__ __forceinline__ BccDraws bcc_draws(uint32_t s, int colour, uint32_t k
 
 // SLAB: the lattice is a z-slab (DevLattice::slab).
 template <bool SLAB>
-__device__ __forceinline__ BccBlock bcc_block(const DevLattice& D, int f, uint32_t s, int colour, const BccDraws& draws)
+__device__ __forceinline__ BccBlock bcc_block(const DevLattice& D, int f, int colour, const BccDraws& draws)
 {
     BccBlock b;
     // block coordinates: same-colour blocks are every other block per axis
@@ -100,7 +100,6 @@ __device__ __forceinline__ BccBlock bcc_block(const DevLattice& D, int f, uint32
     b.Lx = D.L[0];
     b.Ly = D.L[1];
     b.Lz = D.L[2];
-    b.s = s;
 
     // origin shift of sweep s (same for every wave of the sweep)
     const int ox = (int)(((uint64_t)draws.shift[0] * (uint32_t)b.Lx) >> 32);

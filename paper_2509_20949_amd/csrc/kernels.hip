@@ -483,13 +483,12 @@ __device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, u
 // bank conflicts.  Staging, set-up and write-back are about a third of a
 // wave's time in the first generation of a launch.
 // SLAB: the lattice is a z-slab (DevLattice::slab) -- its own instance, so
-// the periodic kernel carries none of the slab's addressing.  WPG: blocks
-// (waves) per workgroup, kWavesPerGroup (5 workgroups, 20 waves per CU,
-// bound by LDS).  Wider workgroups (3 of 7 or 2 of 11 per CU, 21 and 22
-// waves) fill the wave slots of a 512^3 colour launch more evenly but
-// measured no faster: a CU is busy issuing at 20 waves.
-template <int KMAX, int SMAX, bool SLAB, int WPG>
-__global__ __launch_bounds__(kWave * WPG) __attribute__((amdgpu_waves_per_eu(kSweepWavesPerSimd)))
+// the periodic kernel carries none of the slab's addressing.  A workgroup
+// takes kWavesPerGroup blocks, one wave each.  Wider workgroups (3 of 7 or 2
+// of 11 per CU, 21 and 22 waves) fill the wave slots of a 512^3 colour launch
+// more evenly but measured no faster: a CU is busy issuing at 20 waves.
+template <int KMAX, int SMAX, bool SLAB>
+__global__ __launch_bounds__(kWave * kWavesPerGroup) __attribute__((amdgpu_waves_per_eu(kSweepWavesPerSimd)))
 void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __restrict__ items, int n_groups,
                         int t, int colour)
 {
@@ -497,17 +496,17 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     // fits the st64 immediates of ds_read2st64_b32 and row addresses need no
     // base added), then the block images.
     constexpr int kWBytes = wplanes(KMAX, SMAX) * kPlane * 4;
-    __shared__ __attribute__((aligned(16))) uint8_t s_mem[kWBytes + WPG * kWaveLds];
+    __shared__ __attribute__((aligned(16))) uint8_t s_mem[kWBytes + kWavesPerGroup * kWaveLds];
     int32_t* s_w = (int32_t*)s_mem;
     uint8_t* s_lat = s_mem + kWBytes;
 
     const int wave = wave_id();
     const int lane = threadIdx.x % kWave;
-    // group grp of the launch's n_groups (XCD-aware order): work item g of a
-    // batched launch, or blocks WPG g .. WPG g + WPG - 1 of a single lattice
+    // group grp of the launch's n_groups (XCD-aware order): a work item of a
+    // batched launch, or kWavesPerGroup blocks in a row of a single lattice
     const int grp = xcd_group(n_groups);
     if (grp < 0) return;   // no later barrier in a workgroup without a group
-    int li = 0, f = grp * WPG;
+    int li = 0, f = grp * kWavesPerGroup;
     if (items) {
         li = items[grp].lattice;
         f = items[grp].first_block;
@@ -519,11 +518,12 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     // The threshold tables of sweep s stay in global memory (read only for the
     // few draws whose decision needs them), which leaves LDS for five
     // workgroups per CU.
-    constexpr int kWords = wplanes(KMAX, SMAX) * kPlane, kWPer = (kWords + kWave * WPG - 1) / (kWave * WPG);
+    constexpr int kThreads = kWave * kWavesPerGroup;
+    constexpr int kWords = wplanes(KMAX, SMAX) * kPlane, kWPer = (kWords + kThreads - 1) / kThreads;
     int32_t wword[kWPer];
 #pragma unroll
     for (int n = 0; n < kWPer; ++n) {
-        const int k = n * kWave * WPG + (int)threadIdx.x, row = k % kPlane;
+        const int k = n * kThreads + (int)threadIdx.x, row = k % kPlane;
         wword[n] = k < kWords && row < KMAX * KMAX ? D.wtab[row * wrow(KMAX, SMAX) + k / kPlane] : 0;
     }
     int ti = (int)(s - D.tab_s0);
@@ -534,13 +534,13 @@ void sweep_phase_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
     const bool active = f < D.blocks_per_colour;   // wave-uniform; the group's last waves may have no block
     const uint32_t k0 = D.key[0], k1 = D.key[1];
     const BccDraws pb = bcc_draws(s, colour, k0, k1, lane);
-    const BccBlock B = bcc_block<SLAB>(D, active ? f : 0, s, colour, pb);
+    const BccBlock B = bcc_block<SLAB>(D, active ? f : 0, colour, pb);
     uint8_t* lat = s_lat + wave * kWaveLds;
     const bool dot_codes = KMAX <= 5 && D.drop_last == kWtabDot;
     auto put_weights = [&] {
 #pragma unroll
         for (int n = 0; n < kWPer; ++n) {
-            const int k = n * kWave * WPG + (int)threadIdx.x;
+            const int k = n * kThreads + (int)threadIdx.x;
             if (k < kWords) s_w[k] = wword[n];
         }
     };
@@ -663,38 +663,38 @@ int kmax_for(int K)
     return 8;
 }
 
-template <int KMAX, int SMAX, bool SLAB, int WPG>
+template <int KMAX, int SMAX, bool SLAB>
 static hipError_t launch_t(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t,
                            int colour, hipStream_t stream)
 {
-    hipLaunchKernelGGL((sweep_phase_kernel<KMAX, SMAX, SLAB, WPG>), dim3(xcd_grid(n_groups)), dim3(kWave * WPG),
-                       0, stream, d_lat, d_items, n_groups, t, colour);
+    hipLaunchKernelGGL((sweep_phase_kernel<KMAX, SMAX, SLAB>), dim3(xcd_grid(n_groups)),
+                       dim3(kWave * kWavesPerGroup), 0, stream, d_lat, d_items, n_groups, t, colour);
     return hipGetLastError();
 }
 
-template <int KMAX, bool SLAB, int WPG>
+template <int KMAX, bool SLAB>
 static hipError_t launch_k(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t,
                            int colour, int smax, hipStream_t stream)
 {
     switch (smax) {
-    case 1: return launch_t<KMAX, 1, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, stream);
-    case 2: return launch_t<KMAX, 2, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, stream);
-    case 3: return launch_t<KMAX, 3, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, stream);
+    case 1: return launch_t<KMAX, 1, SLAB>(d_lat, d_items, n_groups, t, colour, stream);
+    case 2: return launch_t<KMAX, 2, SLAB>(d_lat, d_items, n_groups, t, colour, stream);
+    case 3: return launch_t<KMAX, 3, SLAB>(d_lat, d_items, n_groups, t, colour, stream);
     }
     return hipErrorInvalidValue;
 }
 
-template <bool SLAB, int WPG>
+template <bool SLAB>
 static hipError_t launch_bcc(const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int t, int colour,
                              int kmax, int smax, hipStream_t stream)
 {
     switch (kmax) {
-    case 2: return launch_k<2, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 3: return launch_k<3, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 4: return launch_k<4, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 5: return launch_k<5, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 6: return launch_k<6, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, smax, stream);
-    case 8: return launch_k<8, SLAB, WPG>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 2: return launch_k<2, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 3: return launch_k<3, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 4: return launch_k<4, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 5: return launch_k<5, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 6: return launch_k<6, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
+    case 8: return launch_k<8, SLAB>(d_lat, d_items, n_groups, t, colour, smax, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -733,8 +733,8 @@ hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkIt
     if (n_blocks <= kSplitBlocks)
         return launch_sweep_split(d_lat, d_items, d_items ? n_groups * kWavesPerGroup : n_blocks, t, colour, kmax, smax,
                                   stream, slab);
-    if (slab) return launch_bcc<true, kWavesPerGroup>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
-    return launch_bcc<false, kWavesPerGroup>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
+    if (slab) return launch_bcc<true>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
+    return launch_bcc<false>(d_lat, d_items, n_groups, t, colour, kmax, smax, stream);
 }
 
 __global__ void species_max_kernel(const uint8_t* __restrict__ g, size_t n, unsigned int* __restrict__ out)

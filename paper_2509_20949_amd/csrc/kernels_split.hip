@@ -143,7 +143,7 @@ void sweep_split_kernel(const DevLattice* __restrict__ lats, const WorkItem* __r
 
     const uint32_t k0 = D.key[0], k1 = D.key[1];
     const BccDraws pb = bcc_draws(s, colour, k0, k1, lane);
-    const BccBlock B = bcc_block<SLAB>(D, f, s, colour, pb);
+    const BccBlock B = bcc_block<SLAB>(D, f, colour, pb);
     const bool dot_codes = KMAX <= 5 && D.drop_last == kWtabDot;
     // the weight planes' words (row-major table -> planes), on their way
     // while the block is set up
