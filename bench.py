@@ -41,11 +41,14 @@ HBM_PEAK = 8.0e12                 # bytes/s
 
 # Algorithmic integer work of one trial (K = 5 species, S = 3 shells), counted
 # in VALU issue slots of one lane (quarter-rate 32x32->64 multiplies = 4,
-# FP64 multiply/convert/compare = 2), the minimum the method needs:
+# FP64 multiply/convert/compare = 2), for a trial taken by itself:
 #   Philox4x32-10, one call per four trials: 10 x (2 x 4 + 2) / 4  = 25
 #   species counts of the 2 x 26 neighbours, one op each           = 52
 #   dE from the counts: 3 shell differences + 15 x (extract + mad) = 33
 #   Metropolis test: 2 FP64 mul + convert + compare                =  8
+# The fraction reported against it compares kernels on one yardstick.  It is
+# no lower bound: trials that share counts with their neighbours along a row,
+# or with their own partner, need fewer than one operation per neighbour.
 OPS_PER_TRIAL = 25 + 52 + 33 + 8          # = 118
 # Algorithmic HBM bytes of one trial: each site is read once and written
 # once per sweep (uint8 species).
@@ -54,20 +57,24 @@ BYTES_PER_TRIAL = 2
 # HBM traffic of one colour launch on the 512^3 lattice, from rocprofv3
 # FETCH_SIZE and WRITE_SIZE scaled by the same counters on a 1 GiB copy
 # (profiles/sweep_phase_bcc512_k5s3_hbm_counters.md).  It describes the
-# kernel built from the sources with this SHA-256 only; for other sources
-# the bench reports traffic as null.
-MEASURED_TRAFFIC = {"sources_sha256": "f5218e65c2804faa71174f8d195441fee5cc1ef2b0da3856c39517a26dc17f76",
-                    "bytes_per_launch": 220116854}
+# kernel built from the sources with this digest only (`--sources-digest`
+# prints it); for other sources the bench reports traffic as null.
+MEASURED_TRAFFIC = {"sources_sha256": "9e95e0f3a90e3547df1c22146ef5c21f8ce31428791ac358e798b26b50ae61f6",
+                    "bytes_per_launch": 220355693}
 KERNEL_SOURCES = ("paper_2509_20949_amd/csrc/kernels.hip", "paper_2509_20949_amd/csrc/bcc_block.h",
                   "paper_2509_20949_amd/csrc/device_common.h", "paper_2509_20949_amd/csrc/smcx_internal.h")
 
 
 def kernel_sources_digest():
+    """SHA-256 of the sweep kernel's sources without comments and spacing, so
+    that an edit of a comment does not part a measurement from its kernel."""
     import hashlib
+    import re
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, f), "rb") as fh:
-            h.update(fh.read())
+        with open(os.path.join(ROOT, f), encoding="utf-8") as fh:
+            code = re.sub(r"//[^\n]*|/\*.*?\*/", "", fh.read(), flags=re.S)   # (no string of these files holds // or /*)
+        h.update(re.sub(r"\s+", " ", code).encode())
     return h.hexdigest()
 
 
@@ -105,6 +112,8 @@ def parse():
     ap.add_argument("--tune-blocks", action="store_true",
                     help="only measure batched throughput over replica edges 16..96 and block widths "
                          "(the measurements behind the library's block-width plan)")
+    ap.add_argument("--sources-digest", action="store_true",
+                    help="only print the digest of the sweep kernel's sources that a traffic measurement belongs to")
     ap.add_argument("--tune-wpg", action="store_true",
                     help="only time the FCC leg's colour launches with 2 and 11 blocks per workgroup "
                          "(the measurements behind the library's workgroup plan)")
@@ -443,6 +452,9 @@ def main():
               "across several GPUs is not implemented", file=sys.stderr)
         sys.exit(2)
 
+    if args.sources_digest:
+        print(kernel_sources_digest())
+        return
     import torch
     from paper_2509_20949_amd import smcx
     from paper_2509_20949_amd import workloads as W
