@@ -217,10 +217,10 @@ __device__ __forceinline__ void accept_bounds(uint32_t u, float c, int& lo, int&
 }
 
 // The Metropolis test of Eq. (3) for the draw u as two edges on float(dE):
-// dE <= lo is accepted and dE > hi rejected without the tables.  From e as in
-// accept_edges: hi = e + 8; lo = e - 8, but at least 0, so that dE <= 0
-// passes, and at most the lower edge of u = 1, which u = 0 (e = +inf, its
-// upper edge too) passes as well.
+// dE <= lo is accepted and dE > hi rejected without the tables.  The edges of
+// accept_edges, the lower one at least 0, so that dE <= 0 passes, and at most
+// 32 c - M, the lower edge of u = 1: where u = 1 passes, u = 0 does too, and
+// above that u = 0, whose upper edge is +inf, reads the table.
 struct Edges {
     float lo, hi;
 };

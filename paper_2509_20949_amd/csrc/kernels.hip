@@ -16,8 +16,8 @@
 namespace smcx {
 
 // Waves per SIMD the BCC sweep kernel is compiled for (registers); LDS
-// (4 block images and the weight planes per workgroup) admits 5 workgroups
-// of 4 waves per CU.
+// (4 block images and the weight planes per workgroup, 28.7 to 32.5 KB)
+// admits 5 workgroups of 4 waves per CU, at K = 7, 8 and S = 3 (34 KB) 4.
 constexpr int kSweepWavesPerSimd = 5;
 
 // Offsets of the first shell from a corner site (body sites at cell offsets
@@ -479,8 +479,8 @@ __device__ __forceinline__ void trial(uint8_t* lat, int ai, uint32_t u, int e, u
 // vector and LDS instructions together.  The launch took 164 us when each
 // trial loaded 32 cells; with the row window (fewer loads, plane sums in place
 // of single counts), scalar decision masks and the set-up reads overlapped it
-// takes 132 us: 108 VALU, 36 LDS and 44 scalar instructions per wave-round, no
-// bank conflicts.  Staging, set-up and write-back are about a third of a
+// takes 134 us (mean of 200 sweeps at 800 K; 138 in the first 20): 108 VALU,
+// 36 LDS and 44 scalar instructions per wave-round, no bank conflicts.  Staging, set-up and write-back are about a third of a
 // wave's time in the first generation of a launch.
 // SLAB: the lattice is a z-slab (DevLattice::slab) -- its own instance, so
 // the periodic kernel carries none of the slab's addressing.  A workgroup
@@ -700,22 +700,30 @@ static hipError_t launch_bcc(const DevLattice* d_lat, const WorkItem* d_items, i
 }
 
 // Colour launches of at most this many blocks give a block four waves
-// (kernels_split.hip).  Their time rises by a step with every 256 blocks (a
-// workgroup to each CU) until three are resident (42 KB of LDS each), while
-// one wave per block takes the same time up to 1,024 blocks (a workgroup of
-// four blocks to each CU): the lines cross between 512 and 513 blocks, at
-// K = 2, S = 1 between 768 and 769.  us per launch, one wave per block
-// against four: K = 5, S = 3: 64 blocks 31.8 and 19.5, 256 32.4 and 20.0, 512
-// 33.2 and 26.5, 576 33.4 and 33.8, 729 33.8 and 33.9, 800 33.9 and 43.7;
-// K = 8, S = 3: 512 45.0 and 37.0, 576 45.0 and 49.0; K = 4, S = 2: 512 28.2
-// and 22.6, 576 28.4 and 27.6; K = 2, S = 1: 729 24.9 and 23.8, 800 25.1 and
-// 28.1.
+// (kernels_split.hip).  Their time rises by a step with every 256 blocks
+// (another workgroup on each CU; LDS holds three, or four where the weight
+// planes are few), while one wave per block takes nearly the same time up to
+// 1,024 blocks (a workgroup of four blocks to each CU).  us per launch on 256
+// CUs, one wave per block against four:
+//   blocks         64           512          576          729          800
+//   K = 5, S = 3   31.0  19.1   32.4  26.1   32.4  33.0   32.9  33.6   32.9  43.0
+//   K = 8, S = 3   43.2  27.0   44.5  36.6   44.4  47.7   44.9  48.2   44.9  63.9
+//   K = 8, S = 2   33.0  21.7   34.5  28.6   34.4  35.7   35.0  36.2   35.1  48.6
+//   K = 5, S = 2   26.6  17.0   28.0  22.6   28.1  27.5   28.7  28.1   28.7  32.9
+//   K = 2, S = 1   22.6  15.4   24.1  19.6   24.1  22.9   24.7  23.5   24.7  27.2
+// The lines cross between 512 and 513 blocks for the heavier trials.  With two
+// shells and K <= 5, or one shell, they cross between 768 and 769: the one
+// line for all leaves 1 to 5 % there to the four waves.
 constexpr int kSplitBlocks = 512;
-// FCC (37 KB of LDS, four workgroups to a CU; kernels_fcc_split.hip), us per
-// launch at K = 5, S = 3, one wave per block against four: 64 blocks 79.6 and
-// 43.0, 256 79.6 and 44.0, 512 80.5 and 58.8, 576 93.8 and 77.7, 729 94.2 and
-// 78.7, 800 94.7 and 96.8, 1,000 95.3 and 97.4, 1,100 100.4 and 117.9.  (K = 3,
-// S = 1: 1,000 66.7 and 58.1, 1,100 66.9 and 72.3.)
+// FCC (35 to 37 KB of LDS, four workgroups to a CU; kernels_fcc_split.hip), us
+// per launch, one wave per block against four:
+//   blocks         64           512          729          800          1,000        1,100
+//   K = 5, S = 3   79.4  42.9   80.4  58.8   94.1  78.4   94.8  96.8   95.4  97.5   100.9 117.8
+//   K = 3, S = 2   60.1  35.2   62.4  45.5   72.4  56.8   72.6  68.1   73.0  68.6   73.5  84.5
+//   K = 3, S = 1   54.9  31.5   56.9  39.5   66.0  48.6   66.0  57.3   66.7  57.9   66.7  71.9
+// At three shells the lines cross between 768 and 769 blocks, with fewer
+// between 1,024 and 1,025: the one line for all leaves 6 (S = 2) to 15 % (S = 1)
+// of such a launch to the four waves.
 constexpr int kSplitBlocksFcc = 768;
 
 hipError_t launch_sweep_phase(int lattice, const DevLattice* d_lat, const WorkItem* d_items, int n_groups, int n_blocks,

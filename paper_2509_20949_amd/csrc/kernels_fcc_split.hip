@@ -3,9 +3,9 @@
 // kernels_split.hip, says why).
 //
 // A launch of few blocks with one wave per block (kernels_fcc.hip) takes 108
-// dependent rounds of about 2,500 cycles: 50 byte reads and some 300
-// instructions one after the other, from code specialised on the partner's
-// direction that does not fit the instruction cache.  Here a lane counts half
+// dependent rounds, each 50 byte reads among some 250 instructions one after
+// the other, from code specialised on the partner's direction that does not
+// fit the instruction cache.  Here a lane counts half
 // of the site's or of the partner's neighbourhood, 21 cells.
 //
 // Image.  Sites are addressed by their doubled local coordinates (X, Y, Z):
@@ -25,7 +25,8 @@
 // 5 for two.
 //
 // Measured (K = 5, S = 3, 24^3 cells, 1 block per colour): 41 us per launch
-// against 113 with one wave per block; a round takes about 750 cycles, some
+// against 75 with one wave per block (113 before that kernel loaded the site
+// and its partner first); a round takes about 750 cycles, some
 // 420 of them issue.
 #include <type_traits>
 

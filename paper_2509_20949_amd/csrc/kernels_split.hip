@@ -3,10 +3,10 @@
 //
 // A colour launch lasts at least as long as one block's 54 rounds, which
 // depend on each other through the lattice.  With one wavefront per block
-// (kernels.hip) a round of a wave alone on its SIMD takes about 1,600 cycles:
-// some 235 instructions issued one after the other and three LDS round trips.
-// Where a launch has fewer blocks than the chip has wave slots, that chain is
-// its whole time.  Here four lanes count the two neighbourhoods of a trial
+// (kernels.hip) a wave alone on its SIMD issues a round's some 190
+// instructions one after the other and waits for its LDS round trips.  Where a
+// launch has fewer blocks than the chip has wave slots, that chain is its whole
+// time.  Here four lanes count the two neighbourhoods of a trial
 // side by side, so that a round is a third as many instructions of each wave,
 // and the block's four waves run on the CU's four SIMDs.  Lane bit 0: the
 // site's neighbourhood or the partner's.  Lane bit 1: one half of it or the
@@ -28,7 +28,8 @@
 // order.  A barrier separates the three z residues.
 //
 // Measured (K = 5, S = 3, 64^3 cells, 27 blocks per colour): 19.5 us per
-// launch against 42.0 with one wave per block; a round takes about 560 cycles,
+// launch against 31.5 with one wave per block (42.0 before that kernel carried
+// a row's cells in registers); a round takes about 560 cycles,
 // 330 of them issue, the rest two LDS round trips.  About 12,000 of the
 // launch's 43,000 cycles are set-up, staging and write-back.
 #include <type_traits>

@@ -740,10 +740,20 @@ hipError_t launch_pair_counts(int lattice, const uint8_t* species, const int32_t
                               unsigned long long* d_counts, hipStream_t stream)
 {
     if (K < 1 || K > kMaxK || S < 1 || S > kMaxS) return hipErrorInvalidValue;
-    // Bit planes for lattices of 2^22 cells and more: below that a launch
-    // has too few tiles to fill the chip, and the per-lane kernel, with a
-    // wavefront per 64 cells of a row, was faster (per call, measured: 128^3
-    // BCC 47 against 55-71 us, 256^3 133 against 107 us).
+    // Bit planes for lattices of 2^22 cells and more (162^3): below that a
+    // launch has few tiles for the chip, each a long chain where many bonds
+    // are counted, and the per-lane kernel has a wavefront for every four
+    // 64-cell pieces of a row.
+    // us per synchronous call, per-lane against bit planes:
+    //   edge               64           96           128          160          192
+    //   BCC, K = 5, S = 3  32.4  54.2   39.1  54.6   43.6  54.1   59.6  53.9   71.3  55.5
+    //   BCC, K = 3, S = 2  30.9  35.2   36.0  35.5   40.0  35.6   52.1  35.7   61.6  36.9
+    //   BCC, K = 2, S = 1  30.5  31.7   35.7  31.8   38.5  31.8   49.7  31.9   58.3  32.3
+    //   FCC, K = 5, S = 3  34.5  83.2   43.7  83.0   50.9  83.4   77.6  83.0   97.5  85.0
+    //   FCC, K = 2, S = 1  30.9  36.3   36.8  36.2   40.5  36.6   54.1  36.7   64.4  37.2
+    // FCC at K = 5, S = 3 crosses near this line, BCC at 3 x 10^6 cells; with
+    // fewer bonds and species the planes win from about 2^20 cells on, and the
+    // one line leaves up to a third of such a call between 2^20 and 2^22 to them.
     const uint64_t plane_bytes = (lattice == 1 ? 4ull : 2ull) * (uint32_t)L[0] * (uint32_t)L[1];
     const uint64_t cells = (uint64_t)(uint32_t)L[0] * (uint32_t)L[1] * (uint32_t)L[2];
     if (K >= 2 && K <= 5 && plane_bytes < (1ull << 32) && cells >= (1ull << 22))

@@ -54,9 +54,9 @@ constexpr int kWtabDot = 2;    // byte-dot digits (KMAX <= 5)
 
 // Running energy (micro-eV, int64) and accepted-swap count (uint64) of one
 // lattice, spread over kSpread slots one cache line apart: the wave of block
-// f adds its totals to slot f % kSpread, so one launch's thousands of
-// device-scope atomics do not all meet on a single address (they serialise
-// there).  The values are the sums over the slots; state_init/state_sum
+// f adds its totals to slot f % kSpread (wave w of a block's four to slot
+// (4 f + w) % kSpread), so one launch's thousands of device-scope atomics do
+// not all meet on a single address (they serialise there).  The values are the sums over the slots; state_init/state_sum
 // (tables.cpp) write and read the host image.
 constexpr int kSpread = 128;
 constexpr int kSlotWords = 8;                        // 64 bytes per slot: energy, accepted, padding

@@ -130,7 +130,7 @@ int build_wtab(const int32_t* epi, int K, int S, int kmax, int smax, int bias, b
 // block (12 cells, the 4 x 4 x 4-lane round) gives the fewest blocks and the
 // most trials per wavefront.  Measured for batched replicas of every edge
 // 16..96 and every B = 4..12 (bench.py --tune-blocks): the widths with the
-// fewest blocks are the fastest at every edge, by 9 % or more, and B = 12
+// fewest blocks are the fastest at every edge, by 16 % or more, and B = 12
 // always gives them.  The choice depends on nothing else, so a trajectory
 // with block = 0 is reproducible.
 int plan_block(int lattice, int L, int K)
@@ -147,8 +147,8 @@ int plan_block(int lattice, int L, int K)
 // slots per CU in workgroups of 2 (LDS-bound), or 11 in one workgroup of 11
 // images (160 KB of LDS): the wide form is taken when it needs fewer
 // generations, e.g. 2,744 blocks (the 336 x 315 x 315 lattice) take one
-// generation of 2,816 slots instead of 1.07 of 2,560 (measured 196 us per
-// launch against 273).  BCC keeps its 4-wave workgroups: on the 512^3
+// generation of 2,816 slots instead of 1.07 of 2,560 (140 us per launch
+// against 181).  BCC keeps its 4-wave workgroups: on the 512^3
 // lattice, workgroups of 7 and 11 blocks (21 and 22 waves per CU) measured
 // no faster.
 int plan_waves_per_group(int lattice, int blocks_per_colour, int n_cu)
